@@ -513,7 +513,9 @@ int wan_block(const ff_dit& m, const Plan& p, void* ws, int i, const void* ctx, 
   gq.sumsq_w = H;
   const float2* rope = reinterpret_cast<const float2*>(at(ws, p.rope));
   QkvArgs qa{};
-  if (c.head_dim == 128 && gemm_sumsq_ok(gq)) {
+  bool fused = false;
+  if (c.head_dim == 128) FF_TRY(gemm_sumsq_pays(gq, &fused));
+  if (fused) {
     FF_TRY(gemm(gq, s));
     qa.dtype = c.dtype;
     qa.B = p.B; qa.n_tok = p.Ni; qa.tok_offset = 0; qa.n_joint = p.Ni; qa.src_rows = p.Ni;

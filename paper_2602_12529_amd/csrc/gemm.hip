@@ -5,8 +5,8 @@
 // tile; its waves split it into wave tiles, each a grid of 32x32 MFMA blocks.
 // Large problems use a 256 x 256 tile computed by eight waves in a compute /
 // memory ping-pong and fed by direct buffer->LDS loads of 64-wide K slabs
-// (gemm_bf16_pp); small ones a 128 x 128 tile staged through registers with two
-// LDS buffers (gemm_bf16_kernel).  gfx950's LDS serves a 16-byte-per-lane read
+// (gemm_bf16_pp); launches of few such tiles a 128 x 128, 192 or 256 tile fed by a deeper ring of
+// direct loads (gemm_bf16_mid).  gfx950's LDS serves a 16-byte-per-lane read
 // for 16 lanes per clock across 64 banks (256 bytes), so LDS rows are stored
 // with their 16-byte chunks permuted by a row-dependent XOR: the fragment reads
 // of 16 consecutive rows land on 16 distinct bank groups.  Tiles are walked a
@@ -82,13 +82,13 @@ __device__ __forceinline__ void epi_store(const GemmParams& p, int64_t m, int64_
   st1<BF16>(p.out, m * p.ldo + n, v);
 }
 
-// Maps the linear workgroup id to a (tile_m, tile_n) pair: first regroup ids
-// so each XCD owns a contiguous range, then walk GROUP_M tile rows at a time.
+// xcd_remap regroups workgroup ids so that each XCD owns a contiguous range; group_order maps a
+// linear id to a (tile_m, tile_n) pair, walking GROUP_M tile rows at a time.
 __device__ __forceinline__ int64_t xcd_remap(int64_t pid, int64_t total) {
   const int64_t full = total / 8 * 8;
   return pid < full ? (pid % 8) * (full / 8) + pid / 8 : pid;
 }
-template <int64_t GROUP_M = 8>
+template <int64_t GROUP_M>
 __device__ __forceinline__ void group_order(int64_t lid, int64_t num_m, int64_t num_n, int64_t& tm, int64_t& tn) {
   const int64_t in_group = GROUP_M * num_n;
   const int64_t gidx = lid / in_group;
@@ -97,10 +97,6 @@ __device__ __forceinline__ void group_order(int64_t lid, int64_t num_m, int64_t 
   const int64_t r = lid % in_group;
   tm = first_m + r % gsize;
   tn = r / gsize;
-}
-__device__ __forceinline__ void tile_coords(int64_t pid, int64_t num_m, int64_t num_n, int64_t& tm,
-                                            int64_t& tn) {
-  group_order(xcd_remap(pid, num_m * num_n), num_m, num_n, tm, tn);
 }
 
 // Up to two GEMM problems with the same tile kernel in one launch (the text and
@@ -123,7 +119,7 @@ struct GemmBatch {
 
 constexpr int BK = 64;
 
-// Epilogue of one wave's FM x FN grid of 32x32 accumulator blocks.  Each block
+// Epilogue of one 32x32 accumulator block (the third column block of a 96-column wave tile).  It
 // goes through a per-wave 32 x 36 float scratch in LDS (the K loop is over, so
 // LDS is free) and comes back row-major: lane l owns row l/2, 16 consecutive
 // columns, so bias, gate and residual are read and the output written with
@@ -188,19 +184,6 @@ __device__ __forceinline__ void epilogue_block(const GemmParams& p, const f32x16
       if (n + e < p.N) epi_store<true, EPI>(p, m, n + e, v[e]);
   }
 }
-
-// All FM x FN blocks of a wave, block (i, j) at rows mw + 32 i, columns nw + 32 j.  The
-// recursion keeps every accumulator index a compile-time constant (a dynamic index would
-// send the whole accumulator array to scratch memory).
-template <int EPI, int FM, int FN, int B = 0>
-__device__ __forceinline__ void epilogue_blocks(const GemmParams& p, const f32x16_t (&acc)[FM][FN], int64_t mw,
-                                                int64_t nw, float* scratch, int lane) {
-  if constexpr (B < FM * FN) {
-    epilogue_block<EPI>(p, acc[B / FN][B % FN], mw + (B / FN) * 32, nw + (B % FN) * 32, scratch, lane);
-    epilogue_blocks<EPI, FM, FN, B + 1>(p, acc, mw, nw, scratch, lane);
-  }
-}
-
 
 // Epilogue of a wave's FM pairs of 32 x 64 accumulator blocks (the two column blocks of one
 // block row; pair i at rows mw + 32 i, columns nw .. nw + 63).  Each pair goes through a per-wave
@@ -478,140 +461,6 @@ __device__ __forceinline__ void epilogue_qkv(const GemmParams& p, const f32x16_t
       }
     }
   }
-}
-
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void gemm_bf16_kernel(GemmParams p) {
-  constexpr int THREADS = WAVES_M * WAVES_N * 64;
-  constexpr int TM = BM / WAVES_M, TN = BN / WAVES_N;
-  constexpr int FM = TM / 32, FN = TN / 32;
-  constexpr int A_LOADS = BM * 8 / THREADS, B_LOADS = BN * 8 / THREADS;
-  static_assert(A_LOADS * THREADS == BM * 8 && B_LOADS * THREADS == BN * 8, "tile/threads mismatch");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  constexpr int STAGE = (BM + BN) * BK * 2;
-
-  const int64_t num_m = (p.M + BM - 1) / BM, num_n = (p.N + BN - 1) / BN;
-  int64_t tm, tn;
-  tile_coords(blockIdx.x, num_m, num_n, tm, tn);
-  const int64_t m0 = tm * BM, n0 = tn * BN;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-
-  // Global loads of this thread: row (tid + i*THREADS)/8, 16-byte chunk tid%8, staged
-  // through registers and written to LDS at chunk ^ ((row >> 1) & 7).  Rows past the
-  // matrix edge are clamped.
-  const int chunk = tid & 7;
-  const bf16_t* a_src[A_LOADS];
-  const bf16_t* b_src[B_LOADS];
-  int a_lds[A_LOADS], b_lds[B_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int row = (tid + i * THREADS) >> 3;
-    const int64_t g = m0 + row < p.M ? m0 + row : p.M - 1;
-    a_src[i] = static_cast<const bf16_t*>(p.A1) + g * p.lda1 + chunk * 8;
-    a_lds[i] = row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
-  }
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) {
-    const int row = (tid + i * THREADS) >> 3;
-    const int64_t g = n0 + row < p.N ? n0 + row : p.N - 1;
-    b_src[i] = static_cast<const bf16_t*>(p.W) + g * p.ldw + chunk * 8;
-    b_lds[i] = BM * BK * 2 + row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
-  }
-
-  f32x16_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  const int frow = lane & 31, fhalf = lane >> 5;
-  // LDS byte offsets of this lane's fragment rows (chunk 0), and the row's swizzle key.
-  int a_frag[FM], b_frag[FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i) a_frag[i] = (wm * TM + i * 32 + frow) * 128;
-#pragma unroll
-  for (int j = 0; j < FN; ++j) b_frag[j] = BM * BK * 2 + (wn * TN + j * 32 + frow) * 128;
-  const int key = (frow >> 1) & 7;   // the same for every fragment row of this lane
-
-  const int64_t KT = p.K / BK;
-  const int64_t KT1 = p.K1 / BK;   // slab at which A switches to the second source
-  u32x4_t ra[A_LOADS], rb[B_LOADS];
-
-  // Issue the global loads of the current source pointers into registers, then
-  // (after the current slab's MFMAs) write them to stage `buf`.
-#define FF_GEMM_ISSUE()                                                                            \
-  _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i) ra[i] = *reinterpret_cast<const u32x4_t*>(a_src[i]); \
-  _Pragma("unroll") for (int i = 0; i < B_LOADS; ++i) rb[i] = *reinterpret_cast<const u32x4_t*>(b_src[i]);
-#define FF_GEMM_COMMIT(buf)                                                                        \
-  {                                                                                                \
-    char* D_ = smem + (buf) * STAGE;                                                               \
-    _Pragma("unroll") for (int i = 0; i < A_LOADS; ++i) *reinterpret_cast<u32x4_t*>(D_ + a_lds[i]) = ra[i]; \
-    _Pragma("unroll") for (int i = 0; i < B_LOADS; ++i) *reinterpret_cast<u32x4_t*>(D_ + b_lds[i]) = rb[i]; \
-  }
-
-  FF_GEMM_ISSUE()
-  FF_GEMM_COMMIT(0)
-  __syncthreads();
-
-  for (int64_t kt = 0; kt < KT; ++kt) {
-    const int buf = static_cast<int>(kt & 1);
-    const bool more = kt + 1 < KT;
-    if (more) {
-      if (kt + 1 == KT1) {
-        // continue K in the second A source
-#pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) {
-          const int row = (tid + i * THREADS) >> 3;
-          const int64_t g = m0 + row < p.M ? m0 + row : p.M - 1;
-          a_src[i] = static_cast<const bf16_t*>(p.A2) + g * p.lda2 + chunk * 8;
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < A_LOADS; ++i) a_src[i] += BK;
-      }
-#pragma unroll
-      for (int i = 0; i < B_LOADS; ++i) b_src[i] += BK;
-      FF_GEMM_ISSUE()
-    }
-    const char* S = smem + buf * STAGE;
-    // Fragments of k16 step ks + 1 are read while the MFMAs of step ks run.
-    bf16x8_t af[2][FM], bfr[2][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) af[0][i] = *reinterpret_cast<const bf16x8_t*>(S + a_frag[i] + ((fhalf ^ key) << 4));
-#pragma unroll
-    for (int j = 0; j < FN; ++j) bfr[0][j] = *reinterpret_cast<const bf16x8_t*>(S + b_frag[j] + ((fhalf ^ key) << 4));
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int cur = ks & 1;
-      if (ks + 1 < BK / 16) {
-        const int coff = (((ks + 1) * 2 + fhalf) ^ key) << 4;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[cur ^ 1][i] = *reinterpret_cast<const bf16x8_t*>(S + a_frag[i] + coff);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[cur ^ 1][j] = *reinterpret_cast<const bf16x8_t*>(S + b_frag[j] + coff);
-      }
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
-    }
-    if (more) {
-      FF_GEMM_COMMIT(buf ^ 1)
-    }
-    __syncthreads();
-  }
-#undef FF_GEMM_ISSUE
-#undef FF_GEMM_COMMIT
-
-  // acc[i][j][r] holds C[row, col] with col = lane % 32 and row = 8 (r / 4) + 4 (lane / 32) + r % 4.
-  __syncthreads();
-  epilogue_blocks<EPI, FM, FN>(p, acc, m0 + wm * TM, n0 + wn * TN,
-                               reinterpret_cast<float*>(smem) + wave * 32 * 36, lane);
 }
 
 // Workgroup barrier that no instruction (memory or not) is scheduled across.
@@ -960,7 +809,8 @@ __device__ __forceinline__ void pp_body(const GemmBatch& batch) {
     }
   }
   if constexpr (EPI == EPI_QKV) {
-    epilogue_qkv<FM, FN>(p, acc, m0 + wm * TM, n0 + wn * TN, smem + wave * QKV_SCRATCH, lane);
+    // An odd number of heads leaves the last tile's second column of waves past the output.
+    if (n0 + wn * TN < p.N) epilogue_qkv<FM, FN>(p, acc, m0 + wm * TM, n0 + wn * TN, smem + wave * QKV_SCRATCH, lane);
   } else if constexpr (EPI == EPI_QKV_GELU) {
     // A wave's 128 columns are all Q/K/V (below 3H) or all MLP input: 3H is a multiple of 128.
     const int64_t mw = m0 + wm * TM, nw = n0 + wn * TN;
@@ -985,6 +835,135 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_pp(GemmBatch batch) {
 template <int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_fp8_pp(GemmBatch batch) {
   pp_body<EPI, 0, true>(batch);
+}
+
+// ------------------------------------------------------------------ bf16, 128 x BN
+// For launches of few 256 x 256 tiles: eight waves, two per SIMD, share a 128 x BN tile.  K advances
+// in slabs of 64 through a ring of STAGES LDS buffers filled by direct loads (stored with the chunk
+// swizzle of the 256 x 256 kernel).  While a wave multiplies slab s from registers it reads slab
+// s + 1's fragments, so a buffer is free one slab before its slab is computed: when the one barrier
+// of slab s opens, slab s + 1 has landed for every wave and slab s's buffer takes the loads of slab
+// s + STAGES.  Loads past the end of K go through an empty buffer resource (zeros, never used), so the
+// number in flight is the same in every slab.
+// What bounds it: the path of the direct loads (about 47 bytes a clock and CU whether they hit L2 or
+// not) takes longer than the MFMAs of a tile this small; with all workgroups reading one tile's
+// panels it runs no faster.  Whole rounds at K = 12288: 0.44, 0.61 and 0.74 us per slab for BN = 128,
+// 192 and 256, where the register-staged 128 x 128 kernel it replaces took 1.1: 1536 x 3072 x 12288
+// 225 -> 126 us, 1536 x 3072 x 3072 65 -> 39 us, 64 x 3072 x 3072 43 -> 26 us.
+template <int BN, int EPI>
+__global__ __launch_bounds__(512, 1) void gemm_bf16_mid(GemmBatch batch) {
+  constexpr int BM = 128, ROWB = 128;
+  constexpr int STAGE = (BM + BN) * ROWB;
+  constexpr int STAGES = 160 * 1024 / STAGE;
+  constexpr int LPW = STAGE / 1024 / 8;                     // 1 KB loads per wave per slab, the first two of A
+  constexpr int FM = BN == 256 ? 2 : 1, FN = BN == 192 ? 3 : 2;   // 32 x 32 blocks of a wave
+  constexpr int WAVES_N = BN / (32 * FN);
+  static_assert(STAGES >= 3 && (BM / (32 * FM)) * WAVES_N == 8, "tile");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // Each XCD takes a contiguous range of tiles, 8 tile rows at a time: 2-4% faster than launch order
+  // with 16 tile rows, level with 4 or 6.
+  const int64_t lid = xcd_remap(blockIdx.x, batch.tiles);
+  const int which = lid >= batch.tiles0 ? 1 : 0;
+  const GemmParams& p = batch.p[which];
+  const int64_t num_m = (p.M + BM - 1) / BM, num_n = (p.N + BN - 1) / BN;
+  int64_t tm, tn;
+  group_order<8>(lid - (which ? batch.tiles0 : 0), num_m, num_n, tm, tn);
+  const int64_t m0 = tm * BM, n0 = tn * BN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int KT = static_cast<int>(p.K / BK), KT1 = static_cast<int>(p.K1 / BK);
+  const bool two = KT1 > 0 && KT1 < KT;
+
+  // Load q of a wave fills rows 64 q + 8 wave .. + 7 of the stacked [A; W] rows of a buffer.
+  const int lrow = 8 * wave + (lane >> 3);
+  const int lck = (lane & 7) ^ ((lrow >> 1) & 7);
+  const char* a1_tile = static_cast<const char*>(p.A1) + m0 * p.lda1 * 2;
+  const char* a2_tile = static_cast<const char*>(p.A2) + m0 * p.lda2 * 2;
+  const char* b_tile = static_cast<const char*>(p.W) + n0 * p.ldw * 2;
+  const int64_t a1_bytes = (p.M - m0) * p.lda1 * 2, a2_bytes = (p.M - m0) * p.lda2 * 2, b_bytes = (p.N - n0) * p.ldw * 2;
+  const uint32_t a1_off = static_cast<uint32_t>(lrow * p.lda1 * 2 + lck * 16);
+  const uint32_t a2_off = static_cast<uint32_t>(lrow * p.lda2 * 2 + lck * 16);
+  const uint32_t b_off = static_cast<uint32_t>(lrow * p.ldw * 2 + lck * 16);
+  const uint32_t smem_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  struct Src {
+    u32x4_t ra, rb;
+    uint32_t ao, step, lds;
+  };
+  const uint32_t bstep = static_cast<uint32_t>(128 * p.ldw);
+  auto source = [&](int s, int buf) {
+    const bool live = s < KT, second = two && s >= KT1;
+    const int64_t da = static_cast<int64_t>(second ? s - KT1 : s) * ROWB, db = static_cast<int64_t>(s) * ROWB;
+    return Src{buffer_rsrc((second ? a2_tile : a1_tile) + da, live ? static_cast<uint64_t>((second ? a2_bytes : a1_bytes) - da) : 0),
+               buffer_rsrc(b_tile + db, live ? static_cast<uint64_t>(b_bytes - db) : 0), second ? a2_off : a1_off,
+               static_cast<uint32_t>(128 * (second ? p.lda2 : p.lda1)), smem_base + buf * STAGE + wave * 1024};
+  };
+  auto issue_one = [&](const Src& c, int q) {
+    if (q < 2) dma_buf16(c.ra, c.ao + q * c.step, c.lds + q * 8192);
+    else dma_buf16(c.rb, b_off + (q - 2) * bstep, c.lds + q * 8192);
+  };
+  auto issue = [&](int s, int buf) {
+    const Src c = source(s, buf);
+#pragma unroll
+    for (int q = 0; q < LPW; ++q) issue_one(c, q);
+  };
+
+  f32x16_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  const int frow = lane & 31, fhalf = lane >> 5;
+  const int key = (frow >> 1) & 7;
+  const int a_frag0 = (wm * 32 * FM + frow) * ROWB, b_frag0 = BM * ROWB + (wn * 32 * FN + frow) * ROWB;
+  bf16x8_t fa[2][4][FM], fb[2][4][FN];   // fragments of two slabs, [k16 step][block]
+  constexpr int FR = FM + FN, NR = 4 * FR, NM = 4 * FM * FN;   // fragments a k16 step, reads and MFMAs a slab
+  auto read = [&](int buf, int n, bf16x8_t (&a)[4][FM], bf16x8_t (&b)[4][FN]) {
+    const int ks = n / FR, f = n % FR;
+    const char* S = smem + buf * STAGE + (((ks * 2 + fhalf) ^ key) << 4);
+    if (f < FM) a[ks][f] = *reinterpret_cast<const bf16x8_t*>(S + a_frag0 + f * 32 * ROWB);
+    else b[ks][f - FM] = *reinterpret_cast<const bf16x8_t*>(S + b_frag0 + (f - FM) * 32 * ROWB);
+  };
+  int buf = 0, next = 1;   // buffers of slabs s and s + 1
+  auto slab = [&](int s, const bf16x8_t (&a)[4][FM], const bf16x8_t (&b)[4][FN], bf16x8_t (&an)[4][FM], bf16x8_t (&bn)[4][FN]) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 2) * LPW) : "memory");   // slab s + 1 has landed
+    wg_barrier();
+    const Src c = source(s + STAGES, buf);
+    // The slab's loads and the next slab's fragment reads are spread over the MFMAs: a burst of loads
+    // from eight waves would hold every wave's MFMAs back until the address unit has taken them all.
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+      const int ks = m / (FM * FN), i = m / FN % FM, j = m % FN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+      for (int n = m * NR / NM; n < (m + 1) * NR / NM; ++n) read(next, n, an, bn);   // past the last slab: not used
+      if ((m + 1) * LPW / NM > m * LPW / NM) issue_one(c, m * LPW / NM);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    buf = next;
+    next = next == STAGES - 1 ? 0 : next + 1;
+  };
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s) issue(s, s);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * LPW) : "memory");   // slab 0 has landed
+  wg_barrier();
+#pragma unroll
+  for (int n = 0; n < NR; ++n) read(0, n, fa[0], fb[0]);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // before the next barrier frees its buffer
+  int s = 0;
+  for (; s + 1 < KT; s += 2) {
+    slab(s, fa[0], fb[0], fa[1], fb[1]);
+    slab(s + 1, fa[1], fb[1], fa[0], fb[0]);
+  }
+  if (s < KT) slab(s, fa[0], fb[0], fa[1], fb[1]);
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // the ring becomes the epilogue's scratch
+  wg_barrier();
+  float* scratch = reinterpret_cast<float*>(smem) + wave * 32 * PAIR_LD;
+  const int64_t mw = m0 + wm * 32 * FM, nw = n0 + wn * 32 * FN;
+  epilogue_pairs<EPI, FM, FN, 0>(p, acc, mw, nw, scratch, lane);
+  if constexpr (FN == 3) epilogue_block<EPI>(p, acc[0][2], mw, nw + 64, scratch, lane);
 }
 
 // ------------------------------------------------------------------ float32
@@ -1034,18 +1013,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
       const int64_t m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
       if (m < p.M && n < p.N) epi_store<false, EPI>(p, m, n, acc[i][j]);
     }
-}
-
-template <int BM, int BN, int WM, int WN, int EPI>
-int launch_bf16(const GemmParams& p, hipStream_t s, const char* name, double flops, double bytes) {
-  constexpr int smem = 2 * (BM + BN) * BK * 2;
-  static std::atomic<uint64_t> limit_set{0};
-  FF_TRY(ensure_smem_limit(reinterpret_cast<const void*>(&gemm_bf16_kernel<BM, BN, WM, WN, EPI>), smem, limit_set));
-  const int64_t tiles = ((p.M + BM - 1) / BM) * ((p.N + BN - 1) / BN);
-  LaunchScope ls(name, s, flops, bytes);
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, EPI>), dim3(static_cast<unsigned>(tiles)),
-                     dim3(WM * WN * 64), smem, s, p);
-  return ls.status();
 }
 
 // Compute units of the current device (one 256 x 256 tile runs per CU at a time).
@@ -1114,7 +1081,52 @@ int launch_pp_batch(const GemmBatch& b0, hipStream_t s, const char* name, double
   return ls.status();
 }
 
-int64_t tiles256(const GemmParams& p) { return ((p.M + 255) / 256) * ((p.N + 255) / 256); }
+int64_t tiles_of(const GemmParams& p, int bm, int bn) { return ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); }
+int64_t tiles256(const GemmParams& p) { return tiles_of(p, 256, 256); }
+
+// Tile of a launch: the one with the smallest expected time, counted as whole rounds of tiles over the
+// CUs, each its slabs and what a round costs besides (first loads, epilogue).  The constants (us on 256
+// CUs) are fits to whole rounds of the gated epilogue at K = 1536 .. 15360, where the model ranks the
+// tiles as measured: 4608 x 3072 x 3072 is 1 round of 256 x 256 (84 us) against 2 of 128 x 256 (95),
+// 1536 x 12288 x 3072 is 3 rounds of 128 x 192 (128 us) against 2 of 256 x 256 (160), and 1000 x 12288
+// x 3072 1 of 256 x 256 (81) against 2 of 128 x 192 (87).
+// With every CU at work the clock drops and a slab takes about a tenth longer.
+constexpr double kPpSlab = 1.40, kPpRound = 14.0, kPpSplitFixup = 15.0, kFullChip = 1.1;
+double pp_us(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws) {
+  const int64_t tiles = tiles256(p0) + (p1 ? tiles256(*p1) : 0), slabs = p0.K / BK, tail = tiles % cus;
+  const double round = slabs * kPpSlab * (tiles >= cus ? kFullChip : 1.0) + kPpRound;
+  if (split_ws && tiles >= cus && tail > 0 && tail <= cus / 2 && slabs >= kSplitMinK && (!p1 || p1->K == p0.K)) {
+    const int64_t parts = cus / tail < kSplitMaxParts ? cus / tail : kSplitMaxParts;   // plan_split's
+    return (tiles / cus) * round + static_cast<double>(slabs) / parts * kPpSlab + kPpRound + kPpSplitFixup;
+  }
+  return (tiles + cus - 1) / cus * round;
+}
+struct TileChoice {
+  int bn;      // 128, 192 or 256: a 128 x bn tile; 0: the 256 x 256 kernel
+  double us;
+};
+TileChoice choose_tile(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws) {
+  struct Kind { int bn; double slab, round; };
+  constexpr Kind kinds[3] = {{256, 0.76, 10.0}, {192, 0.62, 9.0}, {128, 0.45, 8.0}};
+  TileChoice best{0, pp_us(p0, p1, cus, split_ws)};
+  for (const Kind& k : kinds) {
+    const int64_t tiles = tiles_of(p0, 128, k.bn) + (p1 ? tiles_of(*p1, 128, k.bn) : 0);
+    const double slab = k.slab * (tiles >= cus ? kFullChip : 1.0);
+    const double us = (tiles + cus - 1) / cus * (static_cast<double>(p0.K / BK) * slab + k.round);
+    if (us < best.us) best = {k.bn, us};
+  }
+  return best;
+}
+// The 256 x 256 kernel's fused QKV and sum-of-squares epilogues save the passes that otherwise follow
+// the projection (two or three launches of 8-16 us each where it matters); they are used unless a
+// smaller tile is faster by more than that.
+constexpr double kFusedSavesUs = 20.0;
+int fused_pays(const GemmParams& p0, const GemmParams* p1, bool split_ws, bool* out) {
+  int cus = 0;
+  FF_TRY(device_cus(&cus));
+  *out = pp_us(p0, p1, cus, split_ws) <= choose_tile(p0, p1, cus, split_ws).us + kFusedSavesUs;
+  return FF_OK;
+}
 
 template <int EPI>
 int launch_fp8(const GemmParams& p, hipStream_t s, const char* name, double flops, double bytes) {
@@ -1132,21 +1144,40 @@ int launch_fp8(const GemmParams& p, hipStream_t s, const char* name, double flop
   return ls.status();
 }
 
+template <int BN, int EPI>
+int launch_mid(const GemmBatch& b0, bool two, hipStream_t s, const char* name, double flops, double bytes) {
+  constexpr int stage = (128 + BN) * 128, smem = 160 * 1024 / stage * stage;
+  static std::atomic<uint64_t> limit_set{0};
+  FF_TRY(ensure_smem_limit(reinterpret_cast<const void*>(&gemm_bf16_mid<BN, EPI>), smem, limit_set));
+  GemmBatch b = b0;
+  b.tiles0 = tiles_of(b.p[0], 128, BN);
+  b.tiles = b.tiles0 + (two ? tiles_of(b.p[1], 128, BN) : 0);
+  LaunchScope ls(name, s, flops, bytes);
+  hipLaunchKernelGGL((gemm_bf16_mid<BN, EPI>), dim3(static_cast<unsigned>(b.tiles)), dim3(512), smem, s, b);
+  return ls.status();
+}
+
 const char* const kGemmNames[5] = {"gemm_bf16", "gemm_bf16_gelu", "gemm_bf16_gated", "gemm_bf16_qkv",
                                    "gemm_bf16_qkv_gelu"};
 
-// Problems with at least one 256 x 256 tile per CU take the 256 x 256 kernel;
-// smaller ones the 128 x 128 tile, which fills more CUs.
+// One bf16 problem, or two with the same epilogue in one launch.
 template <int EPI>
-int dispatch_bf16(const GemmParams& p, hipStream_t s, double flops, double bytes, void* ws, size_t ws_bytes) {
-  if (tiles256(p) >= 256) {
-    GemmBatch b{};
-    b.p[0] = p;
-    b.p[1] = p;
-    b.tiles0 = b.tiles = tiles256(p);
-    return launch_pp_batch<EPI>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
+int dispatch_bf16(const GemmParams& p0, const GemmParams* p1, hipStream_t s, double flops, double bytes, void* ws,
+                  size_t ws_bytes) {
+  int cus = 0;
+  FF_TRY(device_cus(&cus));
+  GemmBatch b{};
+  b.p[0] = p0;
+  b.p[1] = p1 ? *p1 : p0;
+  switch (choose_tile(p0, p1, cus, ws != nullptr).bn) {
+    case 128: return launch_mid<128, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+    case 192: return launch_mid<192, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+    case 256: return launch_mid<256, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+    default: break;
   }
-  return launch_bf16<128, 128, 2, 2, EPI>(p, s, kGemmNames[EPI], flops, bytes);
+  b.tiles0 = tiles256(p0);
+  b.tiles = b.tiles0 + (p1 ? tiles256(*p1) : 0);
+  return launch_pp_batch<EPI>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
 }
 
 template <int EPI>
@@ -1185,8 +1216,13 @@ GemmParams make_params(const GemmArgs& a) {
 
 bool gemm_sumsq_ok(const GemmArgs& a) {
   return a.dtype == FF_BF16 && a.K % BK == 0 && a.K1 == a.K && a.N % 64 == 0 && a.ldo % 8 == 0 && aligned16(a.out) &&
-         (!a.bias || aligned16(a.bias)) && a.sumsq && a.sumsq_w > 0 && a.sumsq_w % 64 == 0 && 2 * a.sumsq_w <= a.N &&
-         ((a.M + 255) / 256) * ((a.N + 255) / 256) >= 256;
+         (!a.bias || aligned16(a.bias)) && a.sumsq && a.sumsq_w > 0 && a.sumsq_w % 64 == 0 && 2 * a.sumsq_w <= a.N;
+}
+
+int gemm_sumsq_pays(const GemmArgs& a, bool* out) {
+  *out = false;
+  if (!gemm_sumsq_ok(a)) return FF_OK;
+  return fused_pays(make_params(a), nullptr, a.split_ws != nullptr, out);
 }
 
 namespace {
@@ -1221,7 +1257,9 @@ int gemm(const GemmArgs& a, hipStream_t s) {
   if (a.epi == EPI_QKV) {
     GemmParams p = make_params(a);
     const bool tail = a.qkv && a.N > 3 * static_cast<int64_t>(a.qkv->heads) * a.qkv->d;   // MLP columns
-    if (qkv_fusable(a) && a.K % BK == 0 && tiles256(p) >= 256) {
+    bool fuse = qkv_fusable(a) && a.K % BK == 0;
+    if (fuse) FF_TRY(fused_pays(p, nullptr, a.split_ws != nullptr, &fuse));
+    if (fuse) {
       GemmBatch b{};
       b.p[0] = p;
       b.p[1] = p;
@@ -1253,9 +1291,9 @@ int gemm(const GemmArgs& a, hipStream_t s) {
       return fail(FF_EUNSUPPORTED, "gemm: bf16 K=%lld (K1=%lld) must be a multiple of %d", (long long)a.K,
                   (long long)a.K1, BK);
     switch (a.epi) {
-      case EPI_NONE: return dispatch_bf16<EPI_NONE>(p, s, flops, bytes, a.split_ws, a.split_bytes);
-      case EPI_GELU: return dispatch_bf16<EPI_GELU>(p, s, flops, bytes, a.split_ws, a.split_bytes);
-      default: return dispatch_bf16<EPI_GATED>(p, s, flops, bytes, a.split_ws, a.split_bytes);
+      case EPI_NONE: return dispatch_bf16<EPI_NONE>(p, nullptr, s, flops, bytes, a.split_ws, a.split_bytes);
+      case EPI_GELU: return dispatch_bf16<EPI_GELU>(p, nullptr, s, flops, bytes, a.split_ws, a.split_bytes);
+      default: return dispatch_bf16<EPI_GATED>(p, nullptr, s, flops, bytes, a.split_ws, a.split_bytes);
     }
   }
   switch (a.epi) {
@@ -1296,8 +1334,9 @@ int gemm2(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
     b.p[1] = make_params(a1);
     b.tiles0 = tiles256(b.p[0]);
     b.tiles = b.tiles0 + tiles256(b.p[1]);
-    if (a0.epi == EPI_QKV && a1.epi == EPI_QKV && qkv_fusable(a0) && qkv_fusable(a1) && a0.K % BK == 0 &&
-        a1.K % BK == 0 && b.tiles >= 256)
+    bool fuse = qkv_fusable(a0) && qkv_fusable(a1) && a0.K % BK == 0 && a1.K % BK == 0 && a0.K == a1.K && b.tiles > 0;
+    if (fuse) FF_TRY(fused_pays(b.p[0], &b.p[1], a0.split_ws != nullptr, &fuse));
+    if (fuse)
       return launch_pp_batch<EPI_QKV>(b, s, kGemmNames[EPI_QKV], gemm_flops(a0) + gemm_flops(a1),
                                       gemm_bytes(a0) + gemm_bytes(a1), a0.split_ws, a0.split_bytes);
     GemmArgs p0 = a0, p1 = a1;   // two passes for both streams
@@ -1315,20 +1354,12 @@ int gemm2(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
     FF_TRY(gemm(a0, s));
     return gemm(a1, s);
   }
-  GemmBatch b{};
-  b.p[0] = make_params(a0);
-  b.p[1] = make_params(a1);
-  b.tiles0 = tiles256(b.p[0]);
-  b.tiles = b.tiles0 + tiles256(b.p[1]);
-  if (b.tiles < 256) {
-    FF_TRY(gemm(a0, s));
-    return gemm(a1, s);
-  }
+  const GemmParams p0 = make_params(a0), p1 = make_params(a1);
   const double flops = gemm_flops(a0) + gemm_flops(a1), bytes = gemm_bytes(a0) + gemm_bytes(a1);
   switch (a0.epi) {
-    case EPI_NONE: return launch_pp_batch<EPI_NONE>(b, s, kGemmNames[EPI_NONE], flops, bytes, a0.split_ws, a0.split_bytes);
-    case EPI_GELU: return launch_pp_batch<EPI_GELU>(b, s, kGemmNames[EPI_GELU], flops, bytes, a0.split_ws, a0.split_bytes);
-    default: return launch_pp_batch<EPI_GATED>(b, s, kGemmNames[EPI_GATED], flops, bytes, a0.split_ws, a0.split_bytes);
+    case EPI_NONE: return dispatch_bf16<EPI_NONE>(p0, &p1, s, flops, bytes, a0.split_ws, a0.split_bytes);
+    case EPI_GELU: return dispatch_bf16<EPI_GELU>(p0, &p1, s, flops, bytes, a0.split_ws, a0.split_bytes);
+    default: return dispatch_bf16<EPI_GATED>(p0, &p1, s, flops, bytes, a0.split_ws, a0.split_bytes);
   }
 }
 

@@ -430,6 +430,23 @@ def test_fused_qkv_epilogue_ragged_streams(gpu_lib, n_dual, n_single, kernel):
         check(v[b:b + 1], img, C.BF16, model_stages(m), what=f"{w.name} v sample {b}")
 
 
+@pytest.mark.parametrize("heads", [1, 3])
+def test_fused_qkv_epilogue_odd_heads(gpu_lib, heads):
+    """3 x 128 x heads projection columns with an odd number of heads end in the middle of a 256-column
+    tile: the waves past the last column write nothing (they would land on a head of V)."""
+    H = 128 * heads
+    m = C.ModelConfig(model=C.MODEL_MMDIT, io_mode=C.IO_HIDDEN, dtype=C.BF16, n_dual=1, n_single=1, hidden=H,
+                      heads=heads, head_dim=128, mlp_hidden=256, in_channels=64, txt_dim=H, rope_axes=(16, 56, 56))
+    w = C.Workload(name="fused-qkv-odd-heads", index=18, model=m, prompts=2, group=1, grid=(1, 9, 8), n_txt=24,
+                   steps=1, fixed_step=(0.6, 0.5))
+    W, txt, cond, x0, eps = _inputs(w)
+    Wd, T, Cd, X0, E = _device(w, W, txt, cond, x0, eps)
+    res = R.Rollout(w, api.Dit(m, Wd)).run(X0, T, E, cond=Cd, txt_out=torch.empty_like(T))
+    torch.cuda.synchronize()
+    img, _ = odit.forward(m, W, x0, txt, cond=cond, grid=w.grid)
+    check(host(res.vs[0]), img, C.BF16, model_stages(m), what=f"{w.name} {heads} v")
+
+
 @pytest.mark.timeout(900)
 def test_flux_single_block_full_width(gpu_lib):
     """One Flux-shaped single-stream block at full width (H=3072, fused H -> 3H + F projection,

@@ -66,6 +66,18 @@ def test_linear_parity(gpu_lib, M, N, K, dt, epi):
     check(host(out), ref, dt, 0, K, what=f"linear {M}x{N}x{K} {epi}", norm_tol=2e-6 if dt == C.F32 else 6e-3)
 
 
+# Grids that the smaller tiles take, each with 1, 2, 3, 5 and 7 slabs of 64 (fewer and more than the
+# ring's buffers): 128 x 128 tiles (25 of them, ragged edges), 128 x 192 (12 x 16 = 192 of them, where
+# 128 x 128 would take a second round), 128 x 256 (18 x 12 = 216), and 256 x 256 (18 x 12).
+LIN_TILES = [(600, 520), (1530, 3064), (2296, 3064), (4600, 3072)]
+
+
+@pytest.mark.parametrize("M,N", LIN_TILES)
+@pytest.mark.parametrize("slabs,epi", [(1, "bias"), (2, "gated"), (3, "gelu"), (5, "gated"), (7, "bias")])
+def test_linear_tile_choice(gpu_lib, M, N, slabs, epi):
+    test_linear_parity(gpu_lib, M, N, 64 * slabs, C.BF16, epi)
+
+
 # 256 x 256 tiles leaving a partly filled last round on 256 CUs, K of at least 96 slabs of 64:
 # (17 x 16 = 272 tiles, tail 16, split in 8), (17 x 17 = 289, tail 33, split in 7), (33 x 9 = 297
 # with ragged edges, tail 41, split in 6).
