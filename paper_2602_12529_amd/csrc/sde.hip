@@ -509,51 +509,85 @@ __device__ __forceinline__ double adv_value(const float* r, const float* w, int6
   return s;
 }
 
+// One workgroup per group: three passes of its threads over the samples (sums, squared deviations,
+// advantages of the members), each sum reduced over lanes and waves in a fixed order.  Latency bound;
+// a thread per group, walking all N samples by itself, took 143 us a call on 12 groups of 16, this
+// takes 8 (100 groups of 10: 819 and 11).  Group 0's workgroup marks the samples whose group is out of range.
 __global__ __launch_bounds__(kAdvThreads) void group_adv_kernel(const float* __restrict__ rewards,
                                                                 const float* __restrict__ weights,
                                                                 const int32_t* __restrict__ gid, int64_t N, int K,
                                                                 int G, int mode, float eps, float* __restrict__ adv,
                                                                 int32_t* __restrict__ counts) {
-  extern __shared__ double stats[];          // [G * KK] means, then [G * KK] denominators
-  const int KK = mode == 1 ? K : 1;
-  double* s_mean = stats;
-  double* s_den = stats + static_cast<int64_t>(G) * KK;
-  for (int g = threadIdx.x; g < G; g += kAdvThreads) {
-    int32_t cnt = 0;
-    for (int64_t i = 0; i < N; ++i) cnt += (gid[i] == g) ? 1 : 0;
-    if (counts) counts[g] = cnt;
-    for (int j = 0; j < KK; ++j) {
-      double sum = 0.0;
-      for (int64_t i = 0; i < N; ++i)
-        if (gid[i] == g) sum += adv_value(rewards, weights, i, K, mode, j);
-      double mean = cnt ? sum / cnt : 0.0;
-      double ss = 0.0;
-      for (int64_t i = 0; i < N; ++i)
-        if (gid[i] == g) {
-          double d = adv_value(rewards, weights, i, K, mode, j) - mean;
-          ss += d * d;
-        }
-      double sd = cnt ? sqrt(ss / cnt) : 0.0;
-      s_mean[g * KK + j] = mean;
-      s_den[g * KK + j] = sd + static_cast<double>(eps);
-    }
-  }
-  __syncthreads();
+  constexpr int WAVES = kAdvThreads / 64;
+  __shared__ double red[kAdvMaxK][WAVES], s_mean[kAdvMaxK], s_den[kAdvMaxK];
+  __shared__ int32_t red_n[WAVES];
+  const int KK = mode == 1 ? K : 1, g = blockIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double acc[kAdvMaxK];
+  int32_t n = 0;
+#pragma unroll
+  for (int j = 0; j < kAdvMaxK; ++j) acc[j] = 0.0;
   for (int64_t i = threadIdx.x; i < N; i += kAdvThreads) {
-    const int g = gid[i];
-    if (g < 0 || g >= G) {
-      adv[i] = __int_as_float(0x7fc00000);
+    if (gid[i] != g) continue;
+    ++n;
+#pragma unroll
+    for (int j = 0; j < kAdvMaxK; ++j)
+      if (j < KK) acc[j] += adv_value(rewards, weights, i, K, mode, j);
+  }
+  // Wave totals of the live sums, then thread j < KK adds its WAVES of them.
+  auto reduce = [&]() {
+#pragma unroll
+    for (int j = 0; j < kAdvMaxK; ++j)
+      if (j < KK) {
+        const double t = wave_sum(acc[j]);
+        if (lane == 0) red[j][wave] = t;
+      }
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x < KK)
+      for (int w = 0; w < WAVES; ++w) t += red[threadIdx.x][w];
+    return t;
+  };
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+  if (lane == 0) red_n[wave] = n;
+  const double sum = reduce();
+  n = 0;
+  for (int w = 0; w < WAVES; ++w) n += red_n[w];
+  if (threadIdx.x < KK) s_mean[threadIdx.x] = n ? sum / n : 0.0;
+  if (threadIdx.x == 0 && counts) counts[g] = n;
+  __syncthreads();
+  if (n > 0) {   // uniform over the workgroup
+#pragma unroll
+    for (int j = 0; j < kAdvMaxK; ++j) acc[j] = 0.0;
+    for (int64_t i = threadIdx.x; i < N; i += kAdvThreads) {
+      if (gid[i] != g) continue;
+#pragma unroll
+      for (int j = 0; j < kAdvMaxK; ++j)
+        if (j < KK) {
+          const double d = adv_value(rewards, weights, i, K, mode, j) - s_mean[j];
+          acc[j] += d * d;
+        }
+    }
+    const double ss = reduce();
+    if (threadIdx.x < KK) s_den[threadIdx.x] = sqrt(ss / n) + static_cast<double>(eps);
+    __syncthreads();
+  }
+  if (n == 0 && g != 0) return;
+  for (int64_t i = threadIdx.x; i < N; i += kAdvThreads) {
+    const int gi = gid[i];
+    if (gi != g) {
+      if (g == 0 && (gi < 0 || gi >= G)) adv[i] = __int_as_float(0x7fc00000);
       continue;
     }
     double a = 0.0;
     if (mode == 1) {
       for (int j = 0; j < K; ++j) {
-        double w = weights ? static_cast<double>(weights[j]) : 1.0;
-        a += w * (static_cast<double>(rewards[i * K + j]) - s_mean[g * K + j]) / s_den[g * K + j];
+        const double w = weights ? static_cast<double>(weights[j]) : 1.0;
+        a += w * (static_cast<double>(rewards[i * K + j]) - s_mean[j]) / s_den[j];
       }
     } else {
-      double val = adv_value(rewards, weights, i, K, 0, 0);
-      a = (val - s_mean[g]) / s_den[g];
+      a = (adv_value(rewards, weights, i, K, 0, 0) - s_mean[0]) / s_den[0];
     }
     adv[i] = static_cast<float>(a);
   }
@@ -579,8 +613,7 @@ extern "C" int ff_group_advantage(const float* rewards, const float* weights, co
   if (N > 0 && (!rewards || !group_id || !adv)) return fail(FF_EINVAL, "%s: null tensor pointer", fn);
   hipStream_t s = static_cast<hipStream_t>(stream);
   LaunchScope ls("group_advantage", s, 0.0, static_cast<double>(N) * (4.0 * K + 8.0));
-  size_t shm = static_cast<size_t>(n_groups) * KK * 2 * sizeof(double);
-  hipLaunchKernelGGL(group_adv_kernel, dim3(1), dim3(kAdvThreads), shm, s, rewards, weights, group_id, N, K,
-                     n_groups, mode, eps, adv, group_count);
+  hipLaunchKernelGGL(group_adv_kernel, dim3(static_cast<unsigned>(n_groups)), dim3(kAdvThreads), 0, s, rewards,
+                     weights, group_id, N, K, n_groups, mode, eps, adv, group_count);
   return ls.status();
 }
