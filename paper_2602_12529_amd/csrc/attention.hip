@@ -15,8 +15,8 @@
 // 16s + 8(lane/32) + 0..7 in order, exactly the B-operand slots of the second
 // MFMA, so P goes from accumulators to operands without any shuffle.
 //
-// float32 (any d <= 64): one thread per query with the same online softmax,
-// for the small float32 configuration.
+// float32 (any d <= 64): four lanes per query with online softmaxes merged at
+// the end, for the small float32 configuration.
 #include <cmath>
 
 #include "dev.h"
@@ -357,33 +357,81 @@ struct AttnF32Params {
   int64_t q_bs, q_hs, q_rs;
 };
 
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnF32Params p) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * 64 + threadIdx.x;
-  const int64_t bh = blockIdx.y;
-  if (q >= p.n_q) return;
-  constexpr int MAXD = 64;
-  float qv[MAXD], acc[MAXD];
+// A workgroup takes 64 queries of one head, four neighbouring lanes a query: lane c of the four walks
+// keys c, c + 4, ... of 64-key tiles staged in LDS, with q and the output row in registers (DM, the
+// head dimension rounded up, is a compile-time bound; a bound left to run time put both in scratch
+// memory: 77 us on 32 heads of 24 tokens, 7.3 now), and the four online softmaxes are merged.
+template <int DM>
+__global__ __launch_bounds__(256) void attn_f32_kernel(AttnF32Params p) {
+  constexpr int TK = 64, LD = DM + 4;
+  __shared__ __attribute__((aligned(16))) float ks[TK][LD], vs[TK][LD];
+  const int tid = threadIdx.x, c = tid & 3;
+  const int64_t bh = blockIdx.y, q0 = static_cast<int64_t>(blockIdx.x) * 64 + (tid >> 2);
+  const bool live = q0 < p.n_q;
+  const int64_t q = live ? q0 : p.n_q - 1;
   const int d = static_cast<int>(p.d);
   const float* qp = p.Q + (bh / p.heads) * p.q_bs + (bh % p.heads) * p.q_hs + q * p.q_rs;
-  for (int i = 0; i < d; ++i) { qv[i] = qp[i]; acc[i] = 0.f; }
-  float m = -INFINITY, l = 0.f;
-  for (int64_t k = 0; k < p.n_kv; ++k) {
-    const float* kp = p.K + (bh * p.n_kv + k) * d;
-    float sc = 0.f;
-    for (int i = 0; i < d; ++i) sc = fmaf(qv[i], kp[i], sc);
-    sc *= p.scale;
-    const float mn = fmaxf(m, sc);
-    const float alpha = expf(m - mn), e = expf(sc - mn);
-    l = l * alpha + e;
-    const float* vp = p.V + (bh * p.n_kv + k) * d;
-    for (int i = 0; i < d; ++i) acc[i] = fmaf(e, vp[i], acc[i] * alpha);
-    m = mn;
+  float qv[DM], acc[DM];
+#pragma unroll
+  for (int i = 0; i < DM; ++i) {
+    qv[i] = i < d ? qp[i] : 0.f;
+    acc[i] = 0.f;
   }
+  float m = -INFINITY, l = 0.f;
+  for (int64_t k0 = 0; k0 < p.n_kv; k0 += TK) {
+    const int nk = p.n_kv - k0 < TK ? static_cast<int>(p.n_kv - k0) : TK;
+    const float* kp = p.K + (bh * p.n_kv + k0) * d;
+    const float* vp = p.V + (bh * p.n_kv + k0) * d;
+    __syncthreads();
+    for (int e = tid; e < nk * DM; e += 256) {   // columns past d are zero
+      const int r = e / DM, i = e % DM;
+      ks[r][i] = i < d ? kp[r * d + i] : 0.f;
+      vs[r][i] = i < d ? vp[r * d + i] : 0.f;
+    }
+    __syncthreads();
+    for (int k = c; k < nk; k += 4) {
+      float sc = 0.f;
+#pragma unroll
+      for (int i = 0; i < DM; i += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(&ks[k][i]);
+        sc = fmaf(qv[i], x.x, sc);
+        sc = fmaf(qv[i + 1], x.y, sc);
+        sc = fmaf(qv[i + 2], x.z, sc);
+        sc = fmaf(qv[i + 3], x.w, sc);
+      }
+      sc *= p.scale;
+      if (sc == -INFINITY) continue;   // weight 0, also before any finite score
+      const float mn = fmaxf(m, sc);
+      const float alpha = expf(m - mn), e = expf(sc - mn);
+      l = l * alpha + e;
+#pragma unroll
+      for (int i = 0; i < DM; i += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(&vs[k][i]);
+        acc[i] = fmaf(e, x.x, acc[i] * alpha);
+        acc[i + 1] = fmaf(e, x.y, acc[i + 1] * alpha);
+        acc[i + 2] = fmaf(e, x.z, acc[i + 2] * alpha);
+        acc[i + 3] = fmaf(e, x.w, acc[i + 3] * alpha);
+      }
+      m = mn;
+    }
+  }
+  float m_all = fmaxf(m, __shfl_xor(m, 1, 64));
+  m_all = fmaxf(m_all, __shfl_xor(m_all, 2, 64));
+  const float f = m == -INFINITY && l == 0.f ? 0.f : expf(m - m_all);   // a lane without keys adds nothing
+  float l_all = l * f;
+  l_all += __shfl_xor(l_all, 1, 64);
+  l_all += __shfl_xor(l_all, 2, 64);
   const int64_t b = bh / p.heads, h = bh % p.heads;
   float* row = q < p.split ? p.out0 + (b * p.split + q) * p.ldo
                            : p.out1 + (b * (p.n_q - p.split) + (q - p.split)) * p.ldo;
   row += h * d;
-  for (int i = 0; i < d; ++i) row[i] = acc[i] / l;
+#pragma unroll
+  for (int i = 0; i < DM; ++i) {
+    float o = acc[i] * f;
+    o += __shfl_xor(o, 1, 64);
+    o += __shfl_xor(o, 2, 64);
+    if (live && (i & 3) == c && i < d) row[i] = o / l_all;
+  }
 }
 
 }  // namespace
@@ -418,8 +466,10 @@ int attention(const AttnArgs& a, hipStream_t s) {
                   static_cast<const float*>(a.Q), static_cast<const float*>(a.K), static_cast<const float*>(a.Vt),
                   static_cast<float*>(a.out0), static_cast<float*>(a.out1), a.split, a.ldo, a.scale, qbs, qhs, qrs};
   LaunchScope ls("attn_f32", s, flops, bytes);
-  hipLaunchKernelGGL(attn_f32_kernel, dim3(static_cast<unsigned>((a.n_q + 63) / 64), static_cast<unsigned>(a.B * a.heads)),
-                     dim3(64), 0, s, p);
+  const dim3 grid(static_cast<unsigned>((a.n_q + 63) / 64), static_cast<unsigned>(a.B * a.heads));
+  if (a.d <= 16) hipLaunchKernelGGL(attn_f32_kernel<16>, grid, dim3(256), 0, s, p);
+  else if (a.d <= 32) hipLaunchKernelGGL(attn_f32_kernel<32>, grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, p);
   return ls.status();
 }
 

@@ -523,23 +523,23 @@ int norm_dispatch(const NormArgs& a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ QK norm + RoPE + relayout
-// A block handles 64 tokens of one head of one sample; each wave walks 16
-// tokens, lane p owning the rotation pair (2p, 2p+1).  Q and K go to
-// [B, h, n_joint, d]; V goes transposed to [B, h, d, n_joint] through LDS so
-// its rows are written 128 bytes at a time.
-constexpr int kRopeTok = 64;
+// A block handles TOK tokens of one head of one sample, lane p of a wave owning
+// the rotation pair (2p, 2p+1) of a token.  Q and K go to [B, h, n_joint, d]; V
+// goes transposed to [B, h, d, n_joint] through LDS so its rows are written 128
+// bytes at a time (TOK = 64), or as it is (float32: TOK = 4, a token per wave).
+constexpr int kRopeTok = 64, kRopeTokPlain = 4;
 
-template <bool BF16>
+template <bool BF16, int TOK>
 __global__ __launch_bounds__(256) void qk_rope_kernel(QkvArgs a) {
-  __shared__ float vs[kRopeTok][130];
+  __shared__ float vs[TOK][130];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kRopeTok;
+  const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TOK;
   const int h = blockIdx.y;
   const int64_t b = blockIdx.z;
   const int d = a.d, half = d / 2;
   const bool active = lane < half;
   const float inv_d = 1.0f / static_cast<float>(d);
-  for (int tt = wave; tt < kRopeTok; tt += 4) {
+  for (int tt = wave; tt < TOK; tt += 4) {
     const int64_t i = t0 + tt;
     if (i >= a.n_tok) break;
     const int64_t src = (b * a.src_rows + i) * a.ld + static_cast<int64_t>(h) * d + 2 * lane;
@@ -582,10 +582,10 @@ __global__ __launch_bounds__(256) void qk_rope_kernel(QkvArgs a) {
   if (!a.v_transposed) return;
   __syncthreads();
   // Vt[b, h, dd, tok_offset + t0 + tt]
-  const int64_t ntok = (a.n_tok - t0) < kRopeTok ? (a.n_tok - t0) : kRopeTok;
+  const int64_t ntok = (a.n_tok - t0) < TOK ? (a.n_tok - t0) : TOK;
   const int64_t col0 = a.tok_offset + t0;
-  for (int e = threadIdx.x; e < d * kRopeTok; e += 256) {
-    const int dd = e / kRopeTok, tt = e % kRopeTok;
+  for (int e = threadIdx.x; e < d * TOK; e += 256) {
+    const int dd = e / TOK, tt = e % TOK;
     if (tt < ntok) {
       const int64_t o = ((b * a.heads + h) * d + dd) * a.n_joint + col0 + tt;
       st1<BF16>(a.Vt, o, vs[tt][dd]);
@@ -896,8 +896,13 @@ int qk_norm_rope(const QkvArgs& a, hipStream_t s) {
     return fail(FF_EUNSUPPORTED, "qk_norm_rope: precomputed sums need the vector path and the full-width norm");
   LaunchScope ls("qk_norm_rope", s, 0.0, 6.0 * dtype_size(a.dtype) * a.B * a.n_tok * a.heads * a.d);
   if (vec) hipLaunchKernelGGL(qk_rope_vec_kernel, grid, dim3(256), 0, s, a);
-  else if (a.dtype == FF_BF16) hipLaunchKernelGGL(qk_rope_kernel<true>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(qk_rope_kernel<false>, grid, dim3(256), 0, s, a);
+  else if (a.v_transposed && a.dtype == FF_BF16) hipLaunchKernelGGL((qk_rope_kernel<true, kRopeTok>), grid, dim3(256), 0, s, a);
+  else if (a.v_transposed) hipLaunchKernelGGL((qk_rope_kernel<false, kRopeTok>), grid, dim3(256), 0, s, a);
+  else {
+    grid.x = blocks_for(a.n_tok, kRopeTokPlain);
+    if (a.dtype == FF_BF16) hipLaunchKernelGGL((qk_rope_kernel<true, kRopeTokPlain>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((qk_rope_kernel<false, kRopeTokPlain>), grid, dim3(256), 0, s, a);
+  }
   return ls.status();
 }
 

@@ -66,6 +66,14 @@ def test_linear_parity(gpu_lib, M, N, K, dt, epi):
     check(host(out), ref, dt, 0, K, what=f"linear {M}x{N}x{K} {epi}", norm_tol=2e-6 if dt == C.F32 else 6e-3)
 
 
+# float32: rows and columns around the 32-wide tile, K around the 64-wide chunk, and a K whose rows
+# do not start at 16 bytes.
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (31, 33, 63), (65, 32, 130), (128, 64, 256), (40, 96, 68)])
+@pytest.mark.parametrize("epi", ["gelu_from", "gated"])
+def test_linear_f32_edges(gpu_lib, M, N, K, epi):
+    test_linear_parity(gpu_lib, M, N, K, C.F32, epi)
+
+
 # Grids that the smaller tiles take, each with 1, 2, 3, 5 and 7 slabs of 64 (fewer and more than the
 # ring's buffers): 128 x 128 tiles (25 of them, ragged edges), 128 x 192 (12 x 16 = 192 of them, where
 # 128 x 128 would take a second round), 128 x 256 (18 x 12 = 216), and 256 x 256 (18 x 12).
@@ -155,6 +163,13 @@ def test_attention_parity(gpu_lib, B, h, N, dt, d):
     ref = odit.merge_heads(odit.attention(q, k, v))
     # bf16: the probabilities are rounded to bf16 before the P V product (one storage rounding)
     check(host(out), ref, dt, 1, N, what=f"attention {B}x{h}x{N} d{d}", norm_tol=1e-5 if dt == C.F32 else 1e-2)
+
+
+# float32: fewer keys than the lanes of a query, head dimensions below their compile-time bound, one
+# and several 64-key tiles.
+@pytest.mark.parametrize("N,d", [(1, 2), (3, 16), (5, 24), (64, 32), (65, 48), (130, 64)])
+def test_attention_f32_edges(gpu_lib, N, d):
+    test_attention_parity(gpu_lib, 2, 3, N, C.F32, d)
 
 
 def test_attention_cross_shape(gpu_lib):
