@@ -328,8 +328,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void attn_bf16_d128(AttnParams p) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       uint2 w;
-      w.x = uint32_t(f2bf(o[db][4 * u] * inv)) | (uint32_t(f2bf(o[db][4 * u + 1] * inv)) << 16);
-      w.y = uint32_t(f2bf(o[db][4 * u + 2] * inv)) | (uint32_t(f2bf(o[db][4 * u + 3] * inv)) << 16);
+      w.x = f2bf2(o[db][4 * u] * inv, o[db][4 * u + 1] * inv);
+      w.y = f2bf2(o[db][4 * u + 2] * inv, o[db][4 * u + 3] * inv);
       *reinterpret_cast<uint2*>(os + ql * OLD + 32 * db + 8 * u + 4 * g) = w;
     }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

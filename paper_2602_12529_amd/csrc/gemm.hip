@@ -193,8 +193,9 @@ __device__ __forceinline__ void epilogue_block(const GemmParams& p, const f32x16
 // with 16-byte non-temporal stores (the output streams to memory rather than through the caches:
 // -5 to -8% on the write-bound epilogue).  A row stride of 68 floats keeps both the column writes
 // and the 16-byte row reads free of bank conflicts.  Bias and gate (one row when the wave's rows
-// lie in one sample) are loaded once, and each pair's residual rows are issued two pairs ahead,
-// before the previous pair's stores, so no pair waits on the stores of another.
+// lie in one sample) are loaded once, and all residual rows are issued before the first store: loads
+// and stores share one in-order counter, so a load issued behind a pair's stores would wait for them
+// to reach memory.
 constexpr int PAIR_LD = 68;
 __device__ __forceinline__ void transpose_blocks(const f32x16_t& a0, const f32x16_t& a1, float* scratch, int lane,
                                                  float (&v)[4][8]) {
@@ -242,7 +243,7 @@ __device__ __forceinline__ void epilogue_pairs(const GemmParams& p, const f32x16
       cs[0] = c0.x; cs[1] = c0.y; cs[2] = c0.z; cs[3] = c0.w; cs[4] = c1.x; cs[5] = c1.y; cs[6] = c1.z; cs[7] = c1.w;
     }
   }
-  uint4 rs[2][4];     // residual rows of two pairs in flight (bf16)
+  uint4 rs[FM][4];    // residual rows of all pairs (bf16; the K loop's fragment registers)
   auto load_resid = [&](int i, uint4 (&dst)[4]) {
     if (!vec) return;
 #pragma unroll
@@ -255,8 +256,8 @@ __device__ __forceinline__ void epilogue_pairs(const GemmParams& p, const f32x16
   float gv[8];        // gate row of the wave's sample, when its rows lie in one sample
   bool one_sample = false;
   if constexpr (EPI == EPI_GATED) {
-    load_resid(0, rs[0]);
-    if (FM > 1) load_resid(1, rs[1]);
+#pragma unroll
+    for (int i = 0; i < FM; ++i) load_resid(i, rs[i]);
     const int64_t m_lo = mw < p.M ? mw : p.M - 1, m_hi = mw + 32 * FM - 1 < p.M ? mw + 32 * FM - 1 : p.M - 1;
     const uint64_t s_lo = static_cast<uint64_t>(m_lo) / static_cast<uint64_t>(p.rows_per_sample);
     one_sample = s_lo == static_cast<uint64_t>(m_hi) / static_cast<uint64_t>(p.rows_per_sample);
@@ -288,7 +289,7 @@ __device__ __forceinline__ void epilogue_pairs(const GemmParams& p, const f32x16
       if constexpr (SCALED) rsm = p.row_scale[m < p.M ? m : p.M - 1];                                \
       float g[8], r8[8];                                                                             \
       if constexpr (EPI == EPI_GATED) {                                                              \
-        const uint32_t w[4] = {rs[(I) & 1][q].x, rs[(I) & 1][q].y, rs[(I) & 1][q].z, rs[(I) & 1][q].w};  \
+        const uint32_t w[4] = {rs[I][q].x, rs[I][q].y, rs[I][q].z, rs[I][q].w};  \
         for (int j = 0; j < 4; ++j) {                                                                \
           r8[2 * j] = __uint_as_float(w[j] << 16);                                                   \
           r8[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);                                       \
@@ -329,7 +330,6 @@ __device__ __forceinline__ void epilogue_pairs(const GemmParams& p, const f32x16
       }                                                                                              \
       if (m < p.M) st8_bf16_nt(out, m * p.ldo + n, v[q]);                                            \
     }                                                                                                \
-    if constexpr (EPI == EPI_GATED && (I) + 2 < FM) load_resid((I) + 2, rs[(I) & 1]);                 \
   }
   FF_PAIR(0) FF_PAIR(1) FF_PAIR(2) FF_PAIR(3)
 #undef FF_PAIR
@@ -434,8 +434,8 @@ __device__ __forceinline__ void epilogue_qkv(const GemmParams& p, const f32x16_t
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         uint2 w;
-        w.x = uint32_t(f2bf(acc[i][j][4 * g4] + bj)) | (uint32_t(f2bf(acc[i][j][4 * g4 + 1] + bj)) << 16);
-        w.y = uint32_t(f2bf(acc[i][j][4 * g4 + 2] + bj)) | (uint32_t(f2bf(acc[i][j][4 * g4 + 3] + bj)) << 16);
+        w.x = f2bf2(acc[i][j][4 * g4] + bj, acc[i][j][4 * g4 + 1] + bj);
+        w.y = f2bf2(acc[i][j][4 * g4 + 2] + bj, acc[i][j][4 * g4 + 3] + bj);
         *reinterpret_cast<uint2*>(vs + (32 * j + fcol) * VT_LD + 32 * i + 8 * g4 + 4 * fhalf) = w;
       }
   }
