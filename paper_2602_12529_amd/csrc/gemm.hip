@@ -25,6 +25,7 @@
 //
 // f32: a small-tile LDS FMA kernel with the same epilogues, for the float32
 // configurations.
+#include <cmath>
 #include <type_traits>
 
 #include "dev.h"
@@ -529,19 +530,21 @@ __device__ __forceinline__ void xcd_block_order(int64_t lid, int64_t num_m, int6
   tn = 16 * st + 8 * (x >> 2) + (j >> 2);
 }
 
+// BM: 256, or 192 where that leaves the last round of tiles fuller (each wave 96 x 64).
 // LAYOUT 0: each wave a 128 x 64 block (wm = w4 / 2, wn = 2 grp + w4 % 2); LAYOUT 1: a 64 x 128
 // block (wm = w4, wn = grp), one whole 128-column head, for the fused QKV epilogue.  The two
 // waves of a SIMD (same w4) always share their A rows.  F8: operands are E4M3 codes; a slab is
 // 128 of them, read as two k64 steps of 32 bytes per lane (lane half h takes bytes 32 h ..
 // 32 h + 31 of the step, for A and W alike) into the unscaled MFMA 32x32x64.
-template <int EPI, int LAYOUT, bool F8>
+template <int EPI, int LAYOUT, bool F8, int BM = 256>
 __device__ __forceinline__ void pp_body(const GemmBatch& batch) {
   constexpr int ES = F8 ? 1 : 2;                              // bytes per element
-  constexpr int BM = 256, BN = 256, ROWB = 128, KS = ROWB / ES;   // 128-byte LDS rows
-  constexpr int STAGE = (BM + BN) * ROWB;                     // 64 KB
+  constexpr int BN = 256, ROWB = 128, KS = ROWB / ES;         // 128-byte LDS rows
+  constexpr int STAGE = (BM + BN) * ROWB;                     // 64 KB (56 KB)
+  static_assert(BM == 256 || (BM == 192 && LAYOUT == 0 && !F8), "tile rows");
   constexpr int KSTEPS = F8 ? 2 : 4;                          // MFMA k steps per slab
   static_assert(!F8 || (EPI == EPI_NONE || EPI == EPI_GELU), "fp8 epilogues: bias, GELU");
-  constexpr int TM = LAYOUT == 0 ? 128 : 64, TN = LAYOUT == 0 ? 64 : 128;
+  constexpr int TM = LAYOUT == 0 ? BM / 2 : 64, TN = LAYOUT == 0 ? 64 : 128;
   constexpr int FM = TM / 32, FN = TN / 32;
   static_assert((EPI != EPI_QKV && EPI != EPI_QKV_GELU) || LAYOUT == 1, "the fused QKV epilogue needs a head per wave");
   constexpr int A_INS = BM / 8 / 4, B_INS = BN / 8 / 4;       // 1 KB loads per wave per slab
@@ -829,9 +832,9 @@ __device__ __forceinline__ void pp_body(const GemmBatch& batch) {
   }
 }
 
-template <int EPI, int LAYOUT>
+template <int EPI, int LAYOUT, int BM = 256>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_pp(GemmBatch batch) {
-  pp_body<EPI, LAYOUT, false>(batch);
+  pp_body<EPI, LAYOUT, false, BM>(batch);
 }
 template <int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_fp8_pp(GemmBatch batch) {
@@ -1106,21 +1109,21 @@ void plan_split(GemmBatch& b, int cus, void* ws, size_t ws_bytes, int slab_k) {
 
 int64_t split_units(const GemmBatch& b) { return b.split_from + (b.tiles - b.split_from) * b.parts; }
 
-template <int EPI>
+template <int EPI, int BM = 256>
 int launch_pp_batch(const GemmBatch& b0, hipStream_t s, const char* name, double flops, double bytes, void* ws = nullptr,
                     size_t ws_bytes = 0) {
   constexpr bool qkv = EPI == EPI_QKV || EPI == EPI_QKV_GELU;
   constexpr int LAYOUT = qkv ? 1 : 0;
-  constexpr int ring = 2 * 512 * 64 * 2;
+  constexpr int ring = 2 * (BM + 256) * 64 * 2;
   constexpr int smem = qkv && 8 * QKV_SCRATCH > ring ? 8 * QKV_SCRATCH : ring;
   static std::atomic<uint64_t> limit_set{0};
-  FF_TRY(ensure_smem_limit(reinterpret_cast<const void*>(&gemm_bf16_pp<EPI, LAYOUT>), smem, limit_set));
+  FF_TRY(ensure_smem_limit(reinterpret_cast<const void*>(&gemm_bf16_pp<EPI, LAYOUT, BM>), smem, limit_set));
   GemmBatch b = b0;
   int cus = 0;
   FF_TRY(device_cus(&cus));
   plan_split(b, cus, ws, ws_bytes, BK);
   LaunchScope ls(name, s, flops, bytes);
-  hipLaunchKernelGGL((gemm_bf16_pp<EPI, LAYOUT>), dim3(static_cast<unsigned>(split_units(b))), dim3(512), smem, s, b);
+  hipLaunchKernelGGL((gemm_bf16_pp<EPI, LAYOUT, BM>), dim3(static_cast<unsigned>(split_units(b))), dim3(512), smem, s, b);
   return ls.status();
 }
 
@@ -1129,36 +1132,51 @@ int64_t tiles256(const GemmParams& p) { return tiles_of(p, 256, 256); }
 
 // Tile of a launch: the one with the smallest expected time, counted as whole rounds of tiles over the
 // CUs, each its slabs and what a round costs besides (first loads, epilogue).  The constants (us on 256
-// CUs) are fits to whole rounds of the gated epilogue at K = 1536 .. 15360, where the model ranks the
-// tiles as measured: 4608 x 3072 x 3072 is 1 round of 256 x 256 (84 us) against 2 of 128 x 256 (95),
-// 1536 x 12288 x 3072 is 3 rounds of 128 x 192 (128 us) against 2 of 256 x 256 (160), and 1000 x 12288
-// x 3072 1 of 256 x 256 (81) against 2 of 128 x 192 (87).
-// With every CU at work the clock drops and a slab takes about a tenth longer.
-constexpr double kPpSlab = 1.40, kPpRound = 14.0, kPpSplitFixup = 15.0, kFullChip = 1.1;
-double pp_us(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws) {
-  const int64_t tiles = tiles256(p0) + (p1 ? tiles256(*p1) : 0), slabs = p0.K / BK, tail = tiles % cus;
-  const double round = slabs * kPpSlab * (tiles >= cus ? kFullChip : 1.0) + kPpRound;
-  if (split_ws && tiles >= cus && tail > 0 && tail <= cus / 2 && slabs >= kSplitMinK && (!p1 || p1->K == p0.K)) {
-    const int64_t parts = cus / tail < kSplitMaxParts ? cus / tail : kSplitMaxParts;   // plan_split's
-    return (tiles / cus) * round + static_cast<double>(slabs) / parts * kPpSlab + kPpRound + kPpSplitFixup;
-  }
-  return (tiles + cus - 1) / cus * round;
-}
-struct TileChoice {
-  int bn;      // 128, 192 or 256: a 128 x bn tile; 0: the 256 x 256 kernel
-  double us;
+// CUs) are fits to the gated epilogue at K = 1536 .. 15360; a slab takes less when part of the CUs idle,
+// for the clock is higher then.  Measured, us, the chosen one first:
+//   1536 x 3072 x 12288: 128 x 192 121 (one round of 192), 128 x 256 136, 192 x 256 180, 256 x 256 218
+//   4608 x 3072 x 3072:  256 x 256 79 (one round of 216), 128 x 256 90, 128 x 192 112
+//   4000 x 3072 x 15360: 192 x 256 296 (one round of 252), 256 x 256 319 (of 192), 128 x 192 354
+//   6144 x 3072 x 12288: 192 x 256 395 (1.5 rounds, the half one split along K), 256 x 256 434 (1.125)
+//   36864 x 3072 x 12288: 256 x 256 2168, 192 x 256 2280 (more loads per product), 128 x 256 2538
+struct TileKind {
+  int bm, bn;
+  double slab, round;
 };
-TileChoice choose_tile(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws) {
-  struct Kind { int bn; double slab, round; };
-  constexpr Kind kinds[3] = {{256, 0.76, 10.0}, {192, 0.62, 9.0}, {128, 0.45, 8.0}};
-  TileChoice best{0, pp_us(p0, p1, cus, split_ws)};
-  for (const Kind& k : kinds) {
-    const int64_t tiles = tiles_of(p0, 128, k.bn) + (p1 ? tiles_of(*p1, 128, k.bn) : 0);
-    const double slab = k.slab * (tiles >= cus ? kFullChip : 1.0);
-    const double us = (tiles + cus - 1) / cus * (static_cast<double>(p0.K / BK) * slab + k.round);
-    if (us < best.us) best = {k.bn, us};
+constexpr TileKind kTileKinds[5] = {{256, 256, 1.53, 13.0}, {192, 256, 1.22, 10.0}, {128, 256, 0.80, 9.0},
+                                    {128, 192, 0.70, 8.5}, {128, 128, 0.52, 8.0}};
+constexpr double kSplitFixupUs = 15.0, kSplitPartUs = 9.0;
+// plan_split splits the last round of this launch.
+bool splits(const TileKind& k, const GemmParams& p0, const GemmParams* p1, int cus) {
+  const int64_t tiles = tiles_of(p0, k.bm, k.bn) + (p1 ? tiles_of(*p1, k.bm, k.bn) : 0), tail = tiles % cus;
+  return k.bm > 128 && tiles >= cus && tail > 0 && tail <= cus / 2 && p0.K / BK >= kSplitMinK && (!p1 || p1->K == p0.K);
+}
+double tile_us(const TileKind& k, const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws) {
+  const int64_t tiles = tiles_of(p0, k.bm, k.bn) + (p1 ? tiles_of(*p1, k.bm, k.bn) : 0), tail = tiles % cus;
+  const double slabs = static_cast<double>(p0.K / BK);
+  if (split_ws && splits(k, p0, p1, cus)) {
+    const int64_t parts = cus / tail < kSplitMaxParts ? cus / tail : kSplitMaxParts;   // plan_split's
+    return (tiles / cus) * (slabs * k.slab + k.round) + slabs / parts * k.slab + k.round + kSplitFixupUs + kSplitPartUs * (parts - 1);
   }
-  return best;
+  const int64_t rounds = (tiles + cus - 1) / cus;
+  const double fill = static_cast<double>(tiles) / static_cast<double>(rounds * cus);
+  return rounds * (slabs * k.slab * fmax(0.70, 0.51 + 0.49 * fill) + k.round);
+}
+TileKind choose_tile(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws, double* us) {
+  const TileKind* best = &kTileKinds[0];
+  *us = tile_us(*best, p0, p1, cus, split_ws);
+  // Where the 256 x 256 launch's last round can be split, only tiles whose launch can be are compared:
+  // with K that long the smaller ones lose (6144 x 3072 x 12288: 395 and 434 us split, 429 and 463 not).
+  const bool split_only = split_ws && splits(*best, p0, p1, cus);
+  for (const TileKind& k : kTileKinds) {
+    if (split_only && !splits(k, p0, p1, cus)) continue;
+    const double t = tile_us(k, p0, p1, cus, split_ws);
+    if (t < *us) {
+      best = &k;
+      *us = t;
+    }
+  }
+  return *best;
 }
 // The 256 x 256 kernel's fused QKV and sum-of-squares epilogues save the passes that otherwise follow
 // the projection (two or three launches of 8-16 us each where it matters); they are used unless a
@@ -1167,7 +1185,9 @@ constexpr double kFusedSavesUs = 20.0;
 int fused_pays(const GemmParams& p0, const GemmParams* p1, bool split_ws, bool* out) {
   int cus = 0;
   FF_TRY(device_cus(&cus));
-  *out = pp_us(p0, p1, cus, split_ws) <= choose_tile(p0, p1, cus, split_ws).us + kFusedSavesUs;
+  double best;
+  choose_tile(p0, p1, cus, split_ws, &best);
+  *out = tile_us(kTileKinds[0], p0, p1, cus, split_ws) <= best + kFusedSavesUs;
   return FF_OK;
 }
 
@@ -1212,15 +1232,21 @@ int dispatch_bf16(const GemmParams& p0, const GemmParams* p1, hipStream_t s, dou
   GemmBatch b{};
   b.p[0] = p0;
   b.p[1] = p1 ? *p1 : p0;
-  switch (choose_tile(p0, p1, cus, ws != nullptr).bn) {
-    case 128: return launch_mid<128, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
-    case 192: return launch_mid<192, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
-    case 256: return launch_mid<256, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
-    default: break;
+  double us;
+  const TileKind k = choose_tile(p0, p1, cus, ws != nullptr, &us);
+  if (k.bm == 128) {
+    if (k.bn == 128) return launch_mid<128, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+    if (k.bn == 192) return launch_mid<192, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+    return launch_mid<256, EPI>(b, p1 != nullptr, s, kGemmNames[EPI], flops, bytes);
+  }
+  if (k.bm == 192) {
+    b.tiles0 = tiles_of(p0, 192, 256);
+    b.tiles = b.tiles0 + (p1 ? tiles_of(*p1, 192, 256) : 0);
+    return launch_pp_batch<EPI, 192>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
   }
   b.tiles0 = tiles256(p0);
   b.tiles = b.tiles0 + (p1 ? tiles256(*p1) : 0);
-  return launch_pp_batch<EPI>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
+  return launch_pp_batch<EPI, 256>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
 }
 
 // One float32 problem, or two with the same epilogue in one launch.

@@ -76,8 +76,9 @@ def test_linear_f32_edges(gpu_lib, M, N, K, epi):
 
 # Grids that the smaller tiles take, each with 1, 2, 3, 5 and 7 slabs of 64 (fewer and more than the
 # ring's buffers): 128 x 128 tiles (25 of them, ragged edges), 128 x 192 (12 x 16 = 192 of them, where
-# 128 x 128 would take a second round), 128 x 256 (18 x 12 = 216), and 256 x 256 (18 x 12).
-LIN_TILES = [(600, 520), (1530, 3064), (2296, 3064), (4600, 3072)]
+# 128 x 128 would take a second round), 128 x 256 (18 x 12 = 216), 192 x 256 (21 x 12 = 252, ragged
+# rows) and 256 x 256 (18 x 12).
+LIN_TILES = [(600, 520), (1530, 3064), (2296, 3064), (3990, 3072), (4600, 3072)]
 
 
 @pytest.mark.parametrize("M,N", LIN_TILES)
@@ -88,8 +89,8 @@ def test_linear_tile_choice(gpu_lib, M, N, slabs, epi):
 
 # 256 x 256 tiles leaving a partly filled last round on 256 CUs, K of at least 96 slabs of 64:
 # (17 x 16 = 272 tiles, tail 16, split in 8), (17 x 17 = 289, tail 33, split in 7), (33 x 9 = 297
-# with ragged edges, tail 41, split in 6).
-LIN_SPLIT = [(4352, 4096, 6144), (4352, 4352, 12288), (8200, 2100, 6144)]
+# with ragged edges, tail 41, split in 6); 192 x 256 tiles: (32 x 12 = 384, tail 128, split in 2).
+LIN_SPLIT = [(4352, 4096, 6144), (4352, 4352, 12288), (8200, 2100, 6144), (6140, 3072, 12288)]
 
 
 @pytest.mark.parametrize("M,N,K", LIN_SPLIT)
