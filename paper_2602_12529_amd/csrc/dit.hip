@@ -379,9 +379,10 @@ int dual_block(const ff_dit& m, const Plan& p, void* ws, int i, const float* c32
   char* QKV = at(ws, p.qkv);
   char* qkv_k[2] = {QKV, QKV + p.B * p.Nt * 3 * H * es};
   char* U[2] = {at(ws, p.u), at(ws, p.u) + p.B * p.Nt * F * es};
-  for (int k = 0; k < 2; ++k) {
-    FF_TRY(norm_modulate(norm_args(c, rows[k], cur[k], Y + y_off[k] * es, mods[k], mods[k] + H, 6 * H, ntok[k]), s));
-  }
+  NormArgs na[2];
+  for (int k = 0; k < 2; ++k)
+    na[k] = norm_args(c, rows[k], cur[k], Y + y_off[k] * es, mods[k], mods[k] + H, 6 * H, ntok[k]);
+  FF_TRY(norm_modulate2(na[0], na[1], s));
   // QKV projections of both streams; the QK norm, rotation and relayout run in the GEMM epilogue
   // when the shapes allow (gemm2 falls back to a second pass otherwise).
   QkvArgs qa[2];
@@ -402,13 +403,14 @@ int dual_block(const ff_dit& m, const Plan& p, void* ws, int i, const float* c32
   }
   FF_TRY(gemm2(go[0], go[1], s));
   for (int k = 0; k < 2; ++k) {
-    FF_TRY(norm_modulate(norm_args(c, rows[k], dst[k], Y + y_off[k] * es, mods[k] + 3 * H, mods[k] + 4 * H, 6 * H, ntok[k]), s));
+    na[k] = norm_args(c, rows[k], dst[k], Y + y_off[k] * es, mods[k] + 3 * H, mods[k] + 4 * H, 6 * H, ntok[k]);
     g1[k] = gemm_args_ws(p, ws, c.dtype, rows[k], F, H, Y + y_off[k] * es, H, st[k]->mlp1, U[k], F, EPI_GELU);
     g2[k] = gemm_args_ws(p, ws, c.dtype, rows[k], H, F, U[k], F, st[k]->mlp2, dst[k], H, EPI_GATED);
     g2[k].gate = mods[k] + 5 * H; g2[k].gate_ld = 6 * H;
     g2[k].resid = dst[k]; g2[k].ldr = H;
     g2[k].rows_per_sample = ntok[k];
   }
+  FF_TRY(norm_modulate2(na[0], na[1], s));
   FF_TRY(gemm2(g1[0], g1[1], s));
   FF_TRY(gemm2(g2[0], g2[1], s));
   return FF_OK;

@@ -187,6 +187,8 @@ struct NormArgs {
   int64_t rows_per_sample;
 };
 int norm_modulate(const NormArgs& a, hipStream_t s);
+// Two of them, in one launch where they have the same type, width and kind (a dual block's streams).
+int norm_modulate2(const NormArgs& a0, const NormArgs& a1, hipStream_t s);
 
 // Streaming probe (mode 0 read, 1 write, 2 copy) over `chunks` 16-byte words; measurement only.
 int stream_probe(int mode, bool nt, const void* src, void* dst, int64_t chunks, int blocks, hipStream_t s);

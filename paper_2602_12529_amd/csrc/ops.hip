@@ -311,13 +311,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
 // 16-byte vector access.  NCH == 0: generic scalar path, one row per wave.
 constexpr int kNormRows = 4;
 
+// Up to two problems in one launch: workgroups [0, blocks0) belong to a[0].
+struct NormPair {
+  NormArgs a[2];
+  unsigned blocks0;
+};
+
 template <bool BF16, int NCH>
-__global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
+__global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
+  const bool first = blockIdx.x < pair.blocks0;
+  const NormArgs& a = pair.a[first ? 0 : 1];
+  const int64_t block = first ? blockIdx.x : blockIdx.x - pair.blocks0;
   const int lane = threadIdx.x & 63;
   const int64_t H = a.H;
   const float invH = 1.0f / static_cast<float>(H);
   if constexpr (NCH > 0) {
-    const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6)) * kNormRows;
+    const int64_t row0 = (block * 4 + (threadIdx.x >> 6)) * kNormRows;
     float mul[NCH][8], add[NCH][8];
     int64_t cur_b = -1;
     for (int rr = 0; rr < kNormRows; ++rr) {
@@ -380,7 +389,7 @@ __global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
       }
     }
   } else {
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    const int64_t row = block * 4 + (threadIdx.x >> 6);
     if (row >= a.rows) return;
     const int64_t b = row / a.rows_per_sample;
     const float* sh = a.shift ? a.shift + b * a.mod_ld : nullptr;
@@ -417,11 +426,14 @@ __global__ __launch_bounds__(256) void norm_kernel(NormArgs a) {
 // HBM, within noise in the rollout, where the previous GEMM has just written them; non-temporal
 // stores as well were slower.
 template <int NCH, int RPW>
-__global__ __launch_bounds__(256) void norm_lds_kernel(NormArgs a) {
+__global__ __launch_bounds__(256) void norm_lds_kernel(NormPair pair) {
+  const bool first = blockIdx.x < pair.blocks0;
+  const NormArgs& a = pair.a[first ? 0 : 1];
+  const int64_t block = first ? blockIdx.x : blockIdx.x - pair.blocks0;
   extern __shared__ __attribute__((aligned(16))) float mod_s[];   // [2][H]: mul, add
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t H = a.H;
-  const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 4 * RPW;
+  const int64_t r0 = block * 4 * RPW;
   const int64_t b = r0 / a.rows_per_sample;
   float* mul_s = mod_s;
   float* add_s = mod_s + H;
@@ -488,36 +500,57 @@ __global__ __launch_bounds__(256) void norm_lds_kernel(NormArgs a) {
   }
 }
 
+// One problem, or two of the same width in one launch (the streams of a dual block).
 template <bool BF16>
-int norm_dispatch(const NormArgs& a, hipStream_t s) {
-  int nch = 0;
-  const bool mod_ok = (!a.shift || (aligned16(a.shift) && a.mod_ld % 4 == 0)) &&
-                      (!a.scale || (aligned16(a.scale) && a.mod_ld % 4 == 0)) &&
-                      (!a.w || aligned16(a.w)) && (!a.bias || aligned16(a.bias));
-  const bool fits = a.H % 512 == 0 && a.ldx % 8 == 0 && a.ldy % 8 == 0 && aligned16(a.x) && aligned16(a.y) && mod_ok;
-  if (BF16 && fits) nch = static_cast<int>(a.H / 512);
+int norm_dispatch(const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
+  NormPair pr{};
+  pr.a[0] = a0;
+  pr.a[1] = a1 ? *a1 : a0;
+  const int n = a1 ? 2 : 1;
+  int64_t rows = 0;
+  bool fits = BF16, plain = true;
+  for (int i = 0; i < n; ++i) {
+    const NormArgs& a = pr.a[i];
+    rows += a.rows;
+    const bool mod_ok = (!a.shift || (aligned16(a.shift) && a.mod_ld % 4 == 0)) &&
+                        (!a.scale || (aligned16(a.scale) && a.mod_ld % 4 == 0)) &&
+                        (!a.w || aligned16(a.w)) && (!a.bias || aligned16(a.bias));
+    fits = fits && a.H % 512 == 0 && a.ldx % 8 == 0 && a.ldy % 8 == 0 && aligned16(a.x) && aligned16(a.y) && mod_ok;
+    plain = plain && !a.w && !a.bias;
+  }
+  int nch = fits ? static_cast<int>(a0.H / 512) : 0;
   if (nch > 8) nch = 0;
-  const int64_t block_rows = a.rows >= 64 * 512 ? 64 : a.rows >= 32 * 512 ? 32 : 8;
-  const bool one_sample_blocks = a.rows_per_sample % block_rows == 0 || a.rows <= a.rows_per_sample;
-  if (BF16 && nch > 0 && nch <= 6 && one_sample_blocks && !a.w && !a.bias) {
-    const dim3 grid(static_cast<unsigned>((a.rows + block_rows - 1) / block_rows));
-    const size_t shm = 2 * a.H * sizeof(float);
+  // Rows per workgroup, all of one sample: few rows are spread over the CUs, one a wave (512 + 1024 rows
+  // of 3072: 21 us in two launches of two rows a wave, 8.7 us in this one).
+  auto one_sample_blocks = [&](int64_t per) {
+    for (int i = 0; i < n; ++i)
+      if (pr.a[i].rows_per_sample % per != 0 && pr.a[i].rows > pr.a[i].rows_per_sample) return false;
+    return true;
+  };
+  int64_t block_rows = rows >= 64 * 512 ? 64 : rows >= 32 * 512 ? 32 : rows >= 8 * 512 ? 8 : 4;
+  while (block_rows > 4 && !one_sample_blocks(block_rows)) block_rows = block_rows > 8 ? 8 : 4;
+  auto grid_of = [&](int64_t per) {
+    pr.blocks0 = static_cast<unsigned>((a0.rows + per - 1) / per);
+    return dim3(pr.blocks0 + (a1 ? static_cast<unsigned>((a1->rows + per - 1) / per) : 0u));
+  };
+  if (nch > 0 && nch <= 6 && plain && one_sample_blocks(block_rows)) {
+    const dim3 grid = grid_of(block_rows);
+    const size_t shm = 2 * a0.H * sizeof(float);
     switch (nch * 100 + static_cast<int>(block_rows)) {
-#define FF_NL(N, R) case N * 100 + R: hipLaunchKernelGGL((norm_lds_kernel<N, R / 4>), grid, dim3(256), shm, s, a); return FF_OK;
+#define FF_NL(N, R) case N * 100 + R: hipLaunchKernelGGL((norm_lds_kernel<N, R / 4>), grid, dim3(256), shm, s, pr); return FF_OK;
       FF_NL(1, 32) FF_NL(2, 32) FF_NL(3, 32) FF_NL(4, 32) FF_NL(5, 32) FF_NL(6, 32)
+      FF_NL(1, 4) FF_NL(2, 4) FF_NL(3, 4) FF_NL(4, 4) FF_NL(5, 4) FF_NL(6, 4)
       FF_NL(1, 8) FF_NL(2, 8) FF_NL(3, 8) FF_NL(4, 8) FF_NL(5, 8) FF_NL(6, 8)
       FF_NL(1, 64) FF_NL(2, 64) FF_NL(3, 64) FF_NL(4, 64) FF_NL(5, 64) FF_NL(6, 64)
 #undef FF_NL
     }
   }
-  const dim3 grid_rows(static_cast<unsigned>((a.rows + 4 * kNormRows - 1) / (4 * kNormRows)));
+  const dim3 grid = grid_of(nch > 0 ? 4 * kNormRows : 4);
   switch (nch) {
-#define FF_NM(N) case N: hipLaunchKernelGGL((norm_kernel<BF16, N>), grid_rows, dim3(256), 0, s, a); break;
+#define FF_NM(N) case N: hipLaunchKernelGGL((norm_kernel<BF16, N>), grid, dim3(256), 0, s, pr); break;
     FF_NM(1) FF_NM(2) FF_NM(3) FF_NM(4) FF_NM(5) FF_NM(6) FF_NM(7) FF_NM(8)
 #undef FF_NM
-    default:
-      hipLaunchKernelGGL((norm_kernel<BF16, 0>), dim3(static_cast<unsigned>((a.rows + 3) / 4)), dim3(256), 0, s, a);
-      break;
+    default: hipLaunchKernelGGL((norm_kernel<BF16, 0>), grid, dim3(256), 0, s, pr); break;
   }
   return FF_OK;
 }
@@ -868,7 +901,17 @@ int quantize_fp8(int dtype, const void* x, int64_t ldx, void* q, int64_t ldq, fl
 int norm_modulate(const NormArgs& a, hipStream_t s) {
   if (a.rows == 0) return FF_OK;
   LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a.dtype) * a.rows * a.H);
-  FF_TRY(a.dtype == FF_BF16 ? norm_dispatch<true>(a, s) : norm_dispatch<false>(a, s));
+  FF_TRY(a.dtype == FF_BF16 ? norm_dispatch<true>(a, nullptr, s) : norm_dispatch<false>(a, nullptr, s));
+  return ls.status();
+}
+
+int norm_modulate2(const NormArgs& a0, const NormArgs& a1, hipStream_t s) {
+  if (a0.rows == 0 || a1.rows == 0 || a0.dtype != a1.dtype || a0.H != a1.H || a0.norm_kind != a1.norm_kind) {
+    FF_TRY(norm_modulate(a0, s));
+    return norm_modulate(a1, s);
+  }
+  LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a0.dtype) * (a0.rows + a1.rows) * a0.H);
+  FF_TRY(a0.dtype == FF_BF16 ? norm_dispatch<true>(a0, &a1, s) : norm_dispatch<false>(a0, &a1, s));
   return ls.status();
 }
 

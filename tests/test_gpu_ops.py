@@ -258,6 +258,13 @@ def test_norm_modulate_staged_path(gpu_lib, rows, rps):
     check(host(Y), ref, C.BF16, 0, H, what=f"norm_modulate staged {rows} rows", norm_tol=6e-3)
 
 
+# One row a wave below 4096 rows, from one row up; samples of 12 rows keep 4-row blocks where 8 would
+# straddle two of them, also above 4096 rows; samples of 6 straddle those too.
+@pytest.mark.parametrize("rows,rps", [(1, 1), (20, 4), (4092, 12), (4104, 12), (60, 6)])
+def test_norm_modulate_few_rows(gpu_lib, rows, rps):
+    test_norm_modulate_staged_path(gpu_lib, rows, rps)
+
+
 @pytest.mark.parametrize("dt", [C.BF16, C.F32], ids=["bf16", "f32"])
 def test_qk_norm_rope_parity(gpu_lib, dt):
     B, heads, d = 2, 3, 128 if dt == C.BF16 else 16
