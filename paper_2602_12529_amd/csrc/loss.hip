@@ -135,6 +135,48 @@ __global__ __launch_bounds__(256) void loss_finalize(const double* __restrict__ 
   }
 }
 
+// loss_finalize and mean_kernel in one launch: one workgroup, W lanes a sample (a power of two, at most
+// a wave), 1024 / W samples at a time, each sample's partial sums added by stride W and then over the
+// lanes; the samples' results added by thread and then over the workgroup.  All in a fixed order.
+constexpr int kFinThreads = 1024;
+template <bool TWO>
+__global__ __launch_bounds__(kFinThreads) void loss_mean_kernel(const double* __restrict__ partial, int64_t B, int64_t bps,
+                                                                int W, const float* __restrict__ w,
+                                                                double* __restrict__ per_sample, double* __restrict__ loss) {
+  __shared__ double red[kFinThreads / 64];
+  const int lane = threadIdx.x & (W - 1);
+  double sum = 0.0;
+  for (int64_t b0 = 0; b0 < B; b0 += kFinThreads / W) {
+    const int64_t b = b0 + threadIdx.x / W;
+    double s1 = 0.0, s2 = 0.0;
+    if (b < B) {
+#pragma unroll 4
+      for (int64_t i = lane; i < bps; i += W) {
+        s1 += partial[b * bps + i];
+        if constexpr (TWO) s2 += partial[(B + b) * bps + i];
+      }
+    }
+    for (int o = W / 2; o > 0; o >>= 1) {
+      s1 += __shfl_xor(s1, o, 64);
+      if constexpr (TWO) s2 += __shfl_xor(s2, o, 64);
+    }
+    if (b < B && lane == 0) {
+      const double wb = static_cast<double>(w[b]);
+      const double r = TWO ? wb * s1 + (1.0 - wb) * s2 : wb * s1;
+      per_sample[b] = r;
+      sum += r;
+    }
+  }
+  sum = wave_sum(sum);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = 0.0;
+    for (int k = 0; k < kFinThreads / 64; ++k) s += red[k];
+    *loss = s / static_cast<double>(B);
+  }
+}
+
 // loss = (sum_b per_sample[b]) / B, summed in a fixed order.
 __global__ __launch_bounds__(256) void mean_kernel(const double* __restrict__ per_sample, int64_t B,
                                                    double* __restrict__ loss) {
@@ -150,16 +192,17 @@ __global__ __launch_bounds__(256) void mean_kernel(const double* __restrict__ pe
   if (threadIdx.x == 0) *loss = red[0] / static_cast<double>(B);
 }
 
-__global__ __launch_bounds__(256) void grpo_kernel(const double* __restrict__ lpn, const double* __restrict__ lpo,
+constexpr int kGrpoThreads = 1024;   // latency bound: 1920 elements take two steps a thread instead of eight
+__global__ __launch_bounds__(kGrpoThreads) void grpo_kernel(const double* __restrict__ lpn, const double* __restrict__ lpo,
                                                    const float* __restrict__ adv, const float* __restrict__ step_w,
                                                    int64_t B, int S, double clip_eps, double* __restrict__ loss,
                                                    int32_t* __restrict__ n_clipped) {
-  __shared__ double red[256];
-  __shared__ int cnt[256];
+  __shared__ double red[kGrpoThreads];
+  __shared__ int cnt[kGrpoThreads];
   const int64_t n = static_cast<int64_t>(S) * B;
   double s = 0.0;
   int c = 0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) {
+  for (int64_t i = threadIdx.x; i < n; i += kGrpoThreads) {
     const int64_t k = i / B, b = i - k * B;
     const double r = exp(lpn[i] - lpo[i]);
     const double A = static_cast<double>(adv[b]);
@@ -171,7 +214,7 @@ __global__ __launch_bounds__(256) void grpo_kernel(const double* __restrict__ lp
   red[threadIdx.x] = s;
   cnt[threadIdx.x] = c;
   __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
+  for (int k = kGrpoThreads / 2; k > 0; k >>= 1) {
     if (threadIdx.x < k) {
       red[threadIdx.x] += red[threadIdx.x + k];
       cnt[threadIdx.x] += cnt[threadIdx.x + k];
@@ -231,6 +274,16 @@ int matching_loss(const char* fn, const void* a, const void* a2, const void* eps
   }
   {
     LaunchScope ls("loss_finalize", s, 0.0, static_cast<double>(B) * p.bps * 8.0 * (two ? 2.0 : 1.0));
+    // Up to 4096 samples one workgroup finishes everything (192 samples of 32 sums: 9.5 us in two launches,
+    // under 7 in one); more of them are spread over the CUs first.
+    if (B <= 4096) {
+      int W = 1;
+      while (W < 64 && W < p.bps) W *= 2;
+      while (W > 1 && B * W > 2 * kFinThreads) W /= 2;   // two steps over the samples, a lane's loads in flight together
+      if (two) hipLaunchKernelGGL(loss_mean_kernel<true>, dim3(1), dim3(kFinThreads), 0, s, partial, B, p.bps, W, w, per, loss);
+      else hipLaunchKernelGGL(loss_mean_kernel<false>, dim3(1), dim3(kFinThreads), 0, s, partial, B, p.bps, W, w, per, loss);
+      return ls.status();
+    }
     if (two) hipLaunchKernelGGL(loss_finalize<true>, dim3(static_cast<unsigned>(B)), dim3(256), 0, s, partial, B, p.bps, w, per);
     else hipLaunchKernelGGL(loss_finalize<false>, dim3(static_cast<unsigned>(B)), dim3(256), 0, s, partial, B, p.bps, w, per);
     FF_TRY(ls.status());
@@ -305,7 +358,7 @@ int ff_grpo_loss(const double* logp_new, const double* logp_old, const float* ad
   if (!logp_new || !logp_old || !adv || !loss) return fail(FF_EINVAL, "%s: null pointer", fn);
   hipStream_t s = static_cast<hipStream_t>(stream);
   LaunchScope ls("grpo_loss", s, 0.0, static_cast<double>(S) * B * 16.0);
-  hipLaunchKernelGGL(grpo_kernel, dim3(1), dim3(256), 0, s, logp_new, logp_old, adv, step_w, B, S,
+  hipLaunchKernelGGL(grpo_kernel, dim3(1), dim3(kGrpoThreads), 0, s, logp_new, logp_old, adv, step_w, B, S,
                      clip_eps, loss, n_clipped);
   return ls.status();
 }

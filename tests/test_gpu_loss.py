@@ -66,6 +66,12 @@ def test_awm_and_nft_loss_parity(gpu_lib, dt, B, D):
     assert torch.equal(per, per_again) and torch.equal(loss, loss_again)
 
 
+# One workgroup finishes up to 4096 samples, with 64 lanes a sample down to one; more take two launches.
+@pytest.mark.parametrize("B,D", [(1, 200000), (3, 30000), (300, 2056), (4096, 8), (4097, 8)])
+def test_matching_loss_sample_counts(gpu_lib, B, D):
+    test_awm_and_nft_loss_parity(gpu_lib, C.F32, B, D)
+
+
 def test_awm_loss_of_the_exact_velocity_is_zero(gpu_lib):
     """With v = eps - x0 formed on the device the AWM loss vanishes (the sign convention of the target)."""
     B, D = 4, 4096
