@@ -100,6 +100,8 @@ _lock = threading.Lock()
 
 def load() -> ctypes.CDLL:
     global _lib
+    if _lib is not None:   # set once, when every signature is declared
+        return _lib
     with _lock:
         if _lib is not None:
             return _lib

@@ -7,6 +7,7 @@ and the current HIP stream.
 from __future__ import annotations
 
 import ctypes
+import math
 from ctypes import byref, c_double, c_int32, c_int64, c_size_t, c_void_p
 from typing import Dict, Optional, Sequence
 
@@ -26,23 +27,33 @@ def load():
 
 
 def _p(t: Optional[torch.Tensor]):
+    """The tensor's device address; the declared argument types take a plain integer (or None)."""
     if t is None:
         return None
     if not t.is_cuda:
         raise ValueError("expected a device tensor")
-    return c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# torch's current stream as an address.  torch.cuda.current_stream() builds a Stream object for it,
+# 2.8 us a call where the raw accessor takes 0.1 and a small launch 3.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
+
+
+_DTYPE_CODES = {torch.bfloat16: C.BF16, torch.float32: C.F32}
 
 
 def dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.bfloat16:
-        return C.BF16
-    if t.dtype == torch.float32:
-        return C.F32
-    raise ValueError(f"unsupported dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise ValueError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def torch_dtype(code: int):
@@ -57,10 +68,8 @@ def workspace(nbytes: int, device="cuda") -> torch.Tensor:
 
 def _bd(t) -> tuple:
     """(B, D) of a [B, ...] tensor: samples, and elements per sample (also for B = 0)."""
-    d = 1
-    for n in t.shape[1:]:
-        d *= int(n)
-    return int(t.shape[0]), d
+    shape = t.shape
+    return shape[0], math.prod(shape[1:])
 
 
 def sde_workspace_size(B: int, D: int) -> int:
