@@ -794,6 +794,9 @@ __device__ __forceinline__ void pp_body(const GemmBatch& batch) {
         if (__hip_atomic_load(flag + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == batch.epoch) break;
         __builtin_amdgcn_s_sleep(2);
       }
+      // Cleared once seen: a replay of a captured launch carries the same epoch and must not find its
+      // own flag of the replay before.
+      __hip_atomic_store(flag + tid, uint64_t(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
@@ -975,7 +978,8 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_mid(GemmBatch batch) {
 // models are small and latency bound, so a tile's four waves each take a quarter of every 64-wide K
 // chunk (lane: a 4 x 4 block of outputs), the next chunk's loads are in flight meanwhile, and the
 // four partial sums meet in LDS at the end, added in wave order.  128 x 64 x 256 with the gated
-// epilogue: 24.7 us with 64 x 64 tiles walking K by 16, F32_US with these.
+// epilogue: 24.7 us with 64 x 64 tiles walking K by 16; with these, and the text stream's 64 x 64 x 256
+// in the same launch, 9.6.
 constexpr int F32_T = 32, F32_K = 64, F32_LD = F32_T + 4;
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmBatch batch) {

@@ -130,6 +130,30 @@ def test_linear_split_k_tail(gpu_lib, M, N, K, epi):
     check(host(outs[2]), ref, C.BF16, 0, K, what=f"linear unsplit {M}x{N}x{K} {epi}", norm_tol=6e-3)
 
 
+@pytest.mark.parametrize("M,N,K", [(4352, 4096, 6144), (6140, 3072, 12288)])
+def test_linear_split_k_graph_replays(gpu_lib, M, N, K):
+    """A captured launch whose last round is split along K: every replay, on new inputs and with eager
+    launches of the same kernel on the same workspace in between, equals the eager result bit for bit."""
+    say("linear split-K graph", M, N, K)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    draw = lambda *s: torch.randn(s, device="cuda", generator=gen).to(torch.bfloat16)
+    A, W, b = draw(M, K), draw(N, K) * 0.02, draw(N)
+    out, ref = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ws = torch.empty(gpu_lib.linear_workspace_size(), dtype=torch.uint8, device="cuda")
+    gpu_lib.linear(A, W, b, out, ws=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gpu_lib.linear(A, W, b, out, ws=ws)
+    for _ in range(4):
+        A.copy_(draw(M, K))
+        graph.replay()
+        torch.cuda.synchronize()
+        gpu_lib.linear(A, W, b, ref, ws=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+
+
 def test_linear_in_place_gated_residual(gpu_lib):
     M, N, K = 256, 384, 128
     a, w = normal(6, (M, K), C.BF16), normal(7, (N, K), C.BF16, 0.05)
