@@ -848,15 +848,18 @@ __global__ __launch_bounds__(512, 1) void gemm_fp8_pp(GemmBatch batch) {
 // For launches of few 256 x 256 tiles: eight waves, two per SIMD, share a 128 x BN tile.  K advances
 // in slabs of 64 through a ring of STAGES LDS buffers filled by direct loads (stored with the chunk
 // swizzle of the 256 x 256 kernel).  While a wave multiplies slab s from registers it reads slab
-// s + 1's fragments, so a buffer is free one slab before its slab is computed: when the one barrier
-// of slab s opens, slab s + 1 has landed for every wave and slab s's buffer takes the loads of slab
-// s + STAGES.  Loads past the end of K go through an empty buffer resource (zeros, never used), so the
-// number in flight is the same in every slab.
+// s + 1's fragments.  Before the one barrier of slab s each wave waits for its loads of slab s + 1 and
+// for its reads of slab s (issued during slab s - 1); behind it slab s + 1 is there for every wave, no
+// wave reads slab s's buffer any more, and that buffer takes the loads of slab s + STAGES.  Issuing the
+// reads in the first half or three quarters of the MFMAs, to have them back by then, was slower
+// (1536 x 3072 x 12288: 135 and 128 us; spread over all of them 123).  Loads past the end of K go
+// through an empty buffer resource (zeros, never used), so the number in flight is the same in every
+// slab.
 // What bounds it: the path of the direct loads (about 47 bytes a clock and CU whether they hit L2 or
 // not) takes longer than the MFMAs of a tile this small; with all workgroups reading one tile's
-// panels it runs no faster.  Whole rounds at K = 12288: 0.44, 0.61 and 0.74 us per slab for BN = 128,
-// 192 and 256, where the register-staged 128 x 128 kernel it replaces took 1.1: 1536 x 3072 x 12288
-// 225 -> 126 us, 1536 x 3072 x 3072 65 -> 39 us, 64 x 3072 x 3072 43 -> 26 us.
+// panels it runs no faster.  Whole rounds, K = 3072 to 12288: 0.51, 0.69 and 0.84 us per slab for
+// BN = 128, 192 and 256, where the register-staged 128 x 128 kernel it replaces took 0.74 for the
+// first: 1536 x 3072 x 12288 235 -> 123 us, 1536 x 3072 x 3072 65 -> 37 us, 64 x 3072 x 3072 40 -> 25 us.
 template <int BN, int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_mid(GemmBatch batch) {
   constexpr int BM = 128, ROWB = 128;
@@ -935,7 +938,9 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_mid(GemmBatch batch) {
   };
   int buf = 0, next = 1;   // buffers of slabs s and s + 1
   auto slab = [&](int s, const bf16x8_t (&a)[4][FM], const bf16x8_t (&b)[4][FN], bf16x8_t (&an)[4][FM], bf16x8_t (&bn)[4][FN]) {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 2) * LPW) : "memory");   // slab s + 1 has landed
+    // Slab s + 1 has landed, and this wave's reads of slab s have returned: the barrier waits for neither,
+    // and behind it slab s's buffer is refilled.
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((STAGES - 2) * LPW) : "memory");
     wg_barrier();
     const Src c = source(s + STAGES, buf);
     // The slab's loads and the next slab's fragment reads are spread over the MFMAs: a burst of loads
