@@ -118,8 +118,8 @@ struct GemmArgs {
   int64_t sumsq_w = 0;
 };
 // EPI_SUMSQ runs in the 256 x 256 tile kernel only: bf16, N a multiple of 64 and 16-byte aligned rows,
-// sumsq_w a multiple of 64 with 2 sumsq_w <= N.  gemm_sumsq_pays: and it is faster than a plain
-// projection with the norm passes after it.
+// sumsq_w a multiple of 64 with 2 sumsq_w <= N.  gemm_sumsq_pays: and there are at least 256 tiles, or it
+// is faster than a plain projection with the norm passes after it.
 bool gemm_sumsq_ok(const GemmArgs& a);
 int gemm_sumsq_pays(const GemmArgs& a, bool* out);
 // Scratch bytes that let any launch split its last round: 255 tile partials of 256 KB and flags.

@@ -1187,11 +1187,19 @@ TileKind choose_tile(const GemmParams& p0, const GemmParams* p1, int cus, bool s
   }
   return *best;
 }
-// The 256 x 256 kernel's fused QKV and sum-of-squares epilogues save the passes that otherwise follow
-// the projection (two or three launches of 8-16 us each where it matters); they are used unless a
-// smaller tile is faster by more than that.
+// The 256 x 256 kernel's fused QKV and sum-of-squares epilogues take the QK norm of the float32 sums (or
+// round normalised Q and K to bf16 once instead of twice) and save the passes that otherwise follow the
+// projection.  From 256 tiles on they are always used: those passes would round the projection to bf16
+// before its norm, and a tile that fills the last round better gains little or nothing (dual blocks of 3072
+// columns, fused against 192 x 256 or 128 x 256 tiles and a second pass, us: 3392 + 128 rows 1141 and 1109,
+// 2 x (960 + 128) 702 and 713, 1600 + 384 679 and 676; single blocks of 864 rows 364 and 380, 1640 523 and
+// 528).  Below, they are used unless a smaller tile is expected to be faster by more than kFusedSavesUs:
+// 640 + 128 rows 440 fused and 427 in two passes, 768 + 256 442 and 458, 1024 + 512 552 and 579.
 constexpr double kFusedSavesUs = 20.0;
+constexpr int64_t kFusedAlwaysTiles = 256;
 int fused_pays(const GemmParams& p0, const GemmParams* p1, bool split_ws, bool* out) {
+  *out = true;
+  if (tiles256(p0) + (p1 ? tiles256(*p1) : 0) >= kFusedAlwaysTiles) return FF_OK;
   int cus = 0;
   FF_TRY(device_cus(&cus));
   double best;

@@ -430,6 +430,37 @@ def test_fused_qkv_epilogue_ragged_streams(gpu_lib, n_dual, n_single, kernel):
         check(v[b:b + 1], img, C.BF16, model_stages(m), what=f"{w.name} v sample {b}")
 
 
+# 288, 540 and 336, 588 tiles of 256 x 256: rounds that smaller tiles would fill better.
+@pytest.mark.parametrize("n_dual,grid,n_txt,kernel", [(1, (1, 42, 32), 384, "gemm_bf16_qkv"), (1, (1, 53, 64), 128, "gemm_bf16_qkv"),
+                                                      (0, (1, 20, 40), 64, "gemm_bf16_qkv_gelu"),
+                                                      (0, (1, 36, 40), 200, "gemm_bf16_qkv_gelu")])
+def test_qkv_of_256_tiles_is_normed_from_float32(gpu_lib, n_dual, grid, n_txt, kernel):
+    """A QKV projection of at least 256 tiles of 256 x 256 keeps its float32 sums for the QK norm: no packed
+    bf16 projection and no pass over it."""
+    say("fused qkv:", kernel, grid, n_txt)
+    m = C.ModelConfig(model=C.MODEL_MMDIT, io_mode=C.IO_HIDDEN, dtype=C.BF16, n_dual=n_dual, n_single=1 - n_dual, hidden=3072,
+                      heads=24, head_dim=128, mlp_hidden=12288, in_channels=64, txt_dim=3072, rope_axes=(16, 56, 56))
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    draw = lambda *s: torch.randn(s, device="cuda", generator=gen).to(torch.bfloat16)
+    Wd = {name: draw(*shape) * 0.02 + (1.0 if "norm.w" in name else 0.0) for name, shape in api.tensor_table(m)}
+    n_img = grid[1] * grid[2]
+    x, txt, cond = draw(1, n_img, 3072), draw(1, n_txt, 3072), draw(1, 3072)
+    dit = api.Dit(m, Wd)
+    v, txt_out = torch.empty_like(x), torch.empty_like(txt)
+    api.profile_reset()
+    api.profile_enable(True)
+    try:
+        dit.forward(x, txt, grid, v, cond=cond, txt_out=txt_out)
+        torch.cuda.synchronize()
+    finally:
+        api.profile_enable(False)
+    prof = api.profile_read()
+    api.profile_reset()
+    assert prof.get(kernel, {}).get("launches", 0) == 1, sorted(prof)
+    assert "qk_norm_rope" not in prof
+    assert torch.isfinite(v).all() and torch.isfinite(txt_out).all()
+
+
 @pytest.mark.parametrize("heads", [1, 3])
 def test_fused_qkv_epilogue_odd_heads(gpu_lib, heads):
     """3 x 128 x heads projection columns with an odd number of heads end in the middle of a 256-column
