@@ -400,7 +400,11 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnF32Params p) {
         sc = fmaf(qv[i + 3], x.w, sc);
       }
       sc *= p.scale;
-      if (sc == -INFINITY) continue;   // weight 0, also before any finite score
+      if (sc == -INFINITY) {   // weight 0, also before any finite score; 0 times an infinite V is NaN
+#pragma unroll
+        for (int i = 0; i < DM; ++i) acc[i] = fmaf(0.f, vs[k][i], acc[i]);
+        continue;
+      }
       const float mn = fmaxf(m, sc);
       const float alpha = expf(m - mn), e = expf(sc - mn);
       l = l * alpha + e;

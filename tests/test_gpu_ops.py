@@ -197,6 +197,26 @@ def test_attention_f32_edges(gpu_lib, N, d):
     test_attention_parity(gpu_lib, 2, 3, N, C.F32, d)
 
 
+@pytest.mark.parametrize("key", [0, 5, 63, 64, 69])
+def test_attention_f32_weight_zero(gpu_lib, key):
+    """A key whose score is -inf has weight 0, also where it is a lane's first: with a finite V it leaves the
+    softmax of the others, with an infinite one it gives NaN (0 x inf), as the plain product does."""
+    N, d = 70, 16
+    q, k, v = (normal(31 + i, (1, 1, N, d), C.F32) for i in range(3))
+    q[..., 0], k[..., 0] = 1e30, 0.0
+    k[:, :, key, 0] = -1e30
+    keep = [i for i in range(N) if i != key]
+    ref = host(torch.softmax(torch.from_numpy(q[0, 0] @ k[0, 0, keep].T / math.sqrt(d)), -1) @ torch.from_numpy(v[0, 0, keep]))
+    for bad in (1.0, np.inf):
+        v[0, 0, key, 3] = bad
+        out = torch.empty((1, N, d), dtype=torch.float32, device="cuda")
+        gpu_lib.attention(dev(q), dev(k), dev(v), out)
+        got = host(out)[0]
+        assert np.isnan(got[:, 3]).all() if bad == np.inf else np.isfinite(got).all()
+        cols = [i for i in range(d) if bad != np.inf or i != 3]
+        assert rel(got[:, cols], ref[:, cols]) < 1e-5
+
+
 def test_attention_cross_shape(gpu_lib):
     """Queries and keys of different lengths (n_kv with a 64-key tail)."""
     B, h, nq, nkv, d = 1, 2, 300, 136, 128
