@@ -389,32 +389,34 @@ __global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
       }
     }
   } else {
-    const int64_t row = block * 4 + (threadIdx.x >> 6);
-    if (row >= a.rows) return;
-    const int64_t b = row / a.rows_per_sample;
-    const float* sh = a.shift ? a.shift + b * a.mod_ld : nullptr;
-    const float* sc = a.scale ? a.scale + b * a.mod_ld : nullptr;
-    auto finish = [&](int64_t j, float xn) {
-      float mul = sc ? 1.0f + sc[j] : 1.0f;
-      if (a.w) mul *= ld1<BF16>(a.w, j);
-      float add = sh ? sh[j] : 0.0f;
-      if (a.bias) add += ld1<BF16>(a.bias, j);
-      return fmaf(xn, mul, add);
-    };
-    float mean = 0.f;
-    if (a.norm_kind == FF_NORM_LN) {
-      float sum = 0.f;
-      for (int64_t j = lane; j < H; j += 64) sum += ld1<BF16>(a.x, row * a.ldx + j);
-      mean = wave_sum(sum) * invH;
+    // A launch takes fewer than 2^32 threads, so from 2^26 rows on a wave walks several.
+    const int64_t stride = 4 * static_cast<int64_t>(first ? pair.blocks0 : gridDim.x - pair.blocks0);
+    for (int64_t row = block * 4 + (threadIdx.x >> 6); row < a.rows; row += stride) {
+      const int64_t b = row / a.rows_per_sample;
+      const float* sh = a.shift ? a.shift + b * a.mod_ld : nullptr;
+      const float* sc = a.scale ? a.scale + b * a.mod_ld : nullptr;
+      auto finish = [&](int64_t j, float xn) {
+        float mul = sc ? 1.0f + sc[j] : 1.0f;
+        if (a.w) mul *= ld1<BF16>(a.w, j);
+        float add = sh ? sh[j] : 0.0f;
+        if (a.bias) add += ld1<BF16>(a.bias, j);
+        return fmaf(xn, mul, add);
+      };
+      float mean = 0.f;
+      if (a.norm_kind == FF_NORM_LN) {
+        float sum = 0.f;
+        for (int64_t j = lane; j < H; j += 64) sum += ld1<BF16>(a.x, row * a.ldx + j);
+        mean = wave_sum(sum) * invH;
+      }
+      float ss = 0.f;
+      for (int64_t j = lane; j < H; j += 64) {
+        const float d = ld1<BF16>(a.x, row * a.ldx + j) - mean;
+        ss = fmaf(d, d, ss);
+      }
+      const float rstd = rsqrtf(wave_sum(ss) * invH + a.eps);
+      for (int64_t j = lane; j < H; j += 64)
+        st1<BF16>(a.y, row * a.ldy + j, finish(j, (ld1<BF16>(a.x, row * a.ldx + j) - mean) * rstd));
     }
-    float ss = 0.f;
-    for (int64_t j = lane; j < H; j += 64) {
-      const float d = ld1<BF16>(a.x, row * a.ldx + j) - mean;
-      ss = fmaf(d, d, ss);
-    }
-    const float rstd = rsqrtf(wave_sum(ss) * invH + a.eps);
-    for (int64_t j = lane; j < H; j += 64)
-      st1<BF16>(a.y, row * a.ldy + j, finish(j, (ld1<BF16>(a.x, row * a.ldx + j) - mean) * rstd));
   }
 }
 
@@ -500,43 +502,62 @@ __global__ __launch_bounds__(256) void norm_lds_kernel(NormPair pair) {
   }
 }
 
-// One problem, or two of the same width in one launch (the streams of a dual block).
+// How a launch of one problem, or of two of the same width (the streams of a dual block), runs.
+struct NormPlan {
+  int nch;          // 16-byte chunks a lane holds of a row; 0: the element-wise path
+  int block_rows;   // rows per workgroup of norm_lds_kernel; 0: norm_kernel
+};
+constexpr int64_t kNormMaxBlocks = (int64_t(1) << 24) - 1;   // 256 threads each: a launch takes fewer than 2^32
+
 template <bool BF16>
-int norm_dispatch(const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
-  NormPair pr{};
-  pr.a[0] = a0;
-  pr.a[1] = a1 ? *a1 : a0;
-  const int n = a1 ? 2 : 1;
+NormPlan norm_plan(const NormArgs* a, int n) {
   int64_t rows = 0;
   bool fits = BF16, plain = true;
   for (int i = 0; i < n; ++i) {
-    const NormArgs& a = pr.a[i];
-    rows += a.rows;
-    const bool mod_ok = (!a.shift || (aligned16(a.shift) && a.mod_ld % 4 == 0)) &&
-                        (!a.scale || (aligned16(a.scale) && a.mod_ld % 4 == 0)) &&
-                        (!a.w || aligned16(a.w)) && (!a.bias || aligned16(a.bias));
-    fits = fits && a.H % 512 == 0 && a.ldx % 8 == 0 && a.ldy % 8 == 0 && aligned16(a.x) && aligned16(a.y) && mod_ok;
-    plain = plain && !a.w && !a.bias;
+    rows += a[i].rows;
+    const bool mod_ok = (!a[i].shift || (aligned16(a[i].shift) && a[i].mod_ld % 4 == 0)) &&
+                        (!a[i].scale || (aligned16(a[i].scale) && a[i].mod_ld % 4 == 0)) &&
+                        (!a[i].w || aligned16(a[i].w)) && (!a[i].bias || aligned16(a[i].bias));
+    fits = fits && a[i].H % 512 == 0 && a[i].H <= 8 * 512 && a[i].ldx % 8 == 0 && a[i].ldy % 8 == 0 &&
+           aligned16(a[i].x) && aligned16(a[i].y) && mod_ok;
+    plain = plain && !a[i].w && !a[i].bias;
   }
-  int nch = fits ? static_cast<int>(a0.H / 512) : 0;
-  if (nch > 8) nch = 0;
+  NormPlan p{fits ? static_cast<int>(a[0].H / 512) : 0, 0};
+  if (p.nch == 0 || p.nch > 6 || !plain) return p;
   // Rows per workgroup, all of one sample: few rows are spread over the CUs, one a wave (512 + 1024 rows
   // of 3072: 21 us in two launches of two rows a wave, 8.7 us in this one).
-  auto one_sample_blocks = [&](int64_t per) {
+  auto usable = [&](int64_t per) {
+    if (rows / per + n > kNormMaxBlocks) return false;
     for (int i = 0; i < n; ++i)
-      if (pr.a[i].rows_per_sample % per != 0 && pr.a[i].rows > pr.a[i].rows_per_sample) return false;
+      if (a[i].rows_per_sample % per != 0 && a[i].rows > a[i].rows_per_sample) return false;
     return true;
   };
-  int64_t block_rows = rows >= 64 * 512 ? 64 : rows >= 32 * 512 ? 32 : rows >= 8 * 512 ? 8 : 4;
-  while (block_rows > 4 && !one_sample_blocks(block_rows)) block_rows = block_rows > 8 ? 8 : 4;
-  auto grid_of = [&](int64_t per) {
-    pr.blocks0 = static_cast<unsigned>((a0.rows + per - 1) / per);
-    return dim3(pr.blocks0 + (a1 ? static_cast<unsigned>((a1->rows + per - 1) / per) : 0u));
+  const int want = rows >= 64 * 512 ? 64 : rows >= 32 * 512 ? 32 : rows >= 8 * 512 ? 8 : 4;
+  for (int per : {want, 8, 4})
+    if (per <= want && usable(per)) {
+      p.block_rows = per;
+      break;
+    }
+  return p;
+}
+
+template <bool BF16>
+int norm_launch(const NormPlan& p, const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
+  NormPair pr{};
+  pr.a[0] = a0;
+  pr.a[1] = a1 ? *a1 : a0;
+  auto blocks = [&](const NormArgs& a, int64_t per) {
+    const int64_t b = (a.rows + per - 1) / per, most = a1 ? kNormMaxBlocks / 2 : kNormMaxBlocks;
+    return static_cast<unsigned>(b < most ? b : most);   // reached on the element-wise path only, which strides
   };
-  if (nch > 0 && nch <= 6 && plain && one_sample_blocks(block_rows)) {
-    const dim3 grid = grid_of(block_rows);
+  auto grid_of = [&](int64_t per) {
+    pr.blocks0 = blocks(a0, per);
+    return dim3(pr.blocks0 + (a1 ? blocks(*a1, per) : 0u));
+  };
+  if (p.block_rows > 0) {
+    const dim3 grid = grid_of(p.block_rows);
     const size_t shm = 2 * a0.H * sizeof(float);
-    switch (nch * 100 + static_cast<int>(block_rows)) {
+    switch (p.nch * 100 + p.block_rows) {
 #define FF_NL(N, R) case N * 100 + R: hipLaunchKernelGGL((norm_lds_kernel<N, R / 4>), grid, dim3(256), shm, s, pr); return FF_OK;
       FF_NL(1, 32) FF_NL(2, 32) FF_NL(3, 32) FF_NL(4, 32) FF_NL(5, 32) FF_NL(6, 32)
       FF_NL(1, 4) FF_NL(2, 4) FF_NL(3, 4) FF_NL(4, 4) FF_NL(5, 4) FF_NL(6, 4)
@@ -545,8 +566,8 @@ int norm_dispatch(const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
 #undef FF_NL
     }
   }
-  const dim3 grid = grid_of(nch > 0 ? 4 * kNormRows : 4);
-  switch (nch) {
+  const dim3 grid = grid_of(p.nch > 0 ? 4 * kNormRows : 4);
+  switch (p.nch) {
 #define FF_NM(N) case N: hipLaunchKernelGGL((norm_kernel<BF16, N>), grid, dim3(256), 0, s, pr); break;
     FF_NM(1) FF_NM(2) FF_NM(3) FF_NM(4) FF_NM(5) FF_NM(6) FF_NM(7) FF_NM(8)
 #undef FF_NM
@@ -898,20 +919,33 @@ int quantize_fp8(int dtype, const void* x, int64_t ldx, void* q, int64_t ldq, fl
   return ls.status();
 }
 
+namespace {
+template <bool BF16>
+int norm_one(const NormArgs& a, hipStream_t s) {
+  return norm_launch<BF16>(norm_plan<BF16>(&a, 1), a, nullptr, s);
+}
+template <bool BF16>
+int norm_two(const NormArgs& a0, const NormArgs& a1, hipStream_t s) {
+  const NormArgs a[2] = {a0, a1};
+  return norm_launch<BF16>(norm_plan<BF16>(a, 2), a0, &a1, s);
+}
+}  // namespace
+
 int norm_modulate(const NormArgs& a, hipStream_t s) {
   if (a.rows == 0) return FF_OK;
   LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a.dtype) * a.rows * a.H);
-  FF_TRY(a.dtype == FF_BF16 ? norm_dispatch<true>(a, nullptr, s) : norm_dispatch<false>(a, nullptr, s));
+  FF_TRY(a.dtype == FF_BF16 ? norm_one<true>(a, s) : norm_one<false>(a, s));
   return ls.status();
 }
 
 int norm_modulate2(const NormArgs& a0, const NormArgs& a1, hipStream_t s) {
-  if (a0.rows == 0 || a1.rows == 0 || a0.dtype != a1.dtype || a0.H != a1.H || a0.norm_kind != a1.norm_kind) {
+  if (a0.rows == 0 || a1.rows == 0 || a0.dtype != a1.dtype || a0.H != a1.H || a0.norm_kind != a1.norm_kind ||
+      a0.rows + a1.rows > (int64_t(1) << 27)) {
     FF_TRY(norm_modulate(a0, s));
     return norm_modulate(a1, s);
   }
   LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a0.dtype) * (a0.rows + a1.rows) * a0.H);
-  FF_TRY(a0.dtype == FF_BF16 ? norm_dispatch<true>(a0, &a1, s) : norm_dispatch<false>(a0, &a1, s));
+  FF_TRY(a0.dtype == FF_BF16 ? norm_two<true>(a0, a1, s) : norm_two<false>(a0, a1, s));
   return ls.status();
 }
 
@@ -941,7 +975,10 @@ int qk_norm_rope(const QkvArgs& a, hipStream_t s) {
   if (vec) hipLaunchKernelGGL(qk_rope_vec_kernel, grid, dim3(256), 0, s, a);
   else if (a.v_transposed && a.dtype == FF_BF16) hipLaunchKernelGGL((qk_rope_kernel<true, kRopeTok>), grid, dim3(256), 0, s, a);
   else if (a.v_transposed) hipLaunchKernelGGL((qk_rope_kernel<false, kRopeTok>), grid, dim3(256), 0, s, a);
-  else {
+  else if (a.n_tok / kRopeTokPlain >= (int64_t(1) << 24) - 1) {   // a launch takes fewer than 2^32 threads
+    if (a.dtype == FF_BF16) hipLaunchKernelGGL((qk_rope_kernel<true, kRopeTok>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((qk_rope_kernel<false, kRopeTok>), grid, dim3(256), 0, s, a);
+  } else {
     grid.x = blocks_for(a.n_tok, kRopeTokPlain);
     if (a.dtype == FF_BF16) hipLaunchKernelGGL((qk_rope_kernel<true, kRopeTokPlain>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((qk_rope_kernel<false, kRopeTokPlain>), grid, dim3(256), 0, s, a);

@@ -309,6 +309,30 @@ def test_norm_modulate_few_rows(gpu_lib, rows, rps):
     test_norm_modulate_staged_path(gpu_lib, rows, rps)
 
 
+# A launch takes fewer than 2^32 threads: 4 rows (or tokens) a workgroup of 256 end at 2^26 of them.
+@pytest.mark.parametrize("H,rps,dt", [(512, 12, C.BF16), (8, 12, C.F32)])
+def test_norm_modulate_many_rows(gpu_lib, H, rps, dt):
+    rows = (1 << 26) + 44
+    say("norm rows", rows, H)
+    x = torch.full((rows, H), 2.0, dtype=torch.bfloat16 if dt == C.BF16 else torch.float32, device="cuda")
+    gpu_lib.norm_modulate(x, x, rows_per_sample=rps)
+    torch.cuda.synchronize()
+    for r in (0, rows // 2, (1 << 26) - 1, 1 << 26, rows - 1):
+        assert torch.allclose(x[r].float(), torch.ones(H, device="cuda"), rtol=1e-5), r
+
+
+def test_qk_norm_rope_many_tokens(gpu_lib):
+    n = (1 << 26) + 44
+    say("rope tokens", n)
+    qkv = torch.full((1, n, 6), 3.0, device="cuda")
+    w = torch.ones(2, device="cuda")
+    Q, K, V = (torch.zeros((1, 1, n, 2), device="cuda") for _ in range(3))
+    gpu_lib.qk_norm_rope(qkv, 1, 2, w, w, Q, K, V, n, 0)
+    torch.cuda.synchronize()
+    for t, want in ((Q, 1.0), (K, 1.0), (V, 3.0)):
+        assert torch.allclose(t[0, 0], torch.full((2,), want, device="cuda"), rtol=1e-5)
+
+
 @pytest.mark.parametrize("dt", [C.BF16, C.F32], ids=["bf16", "f32"])
 def test_qk_norm_rope_parity(gpu_lib, dt):
     B, heads, d = 2, 3, 128 if dt == C.BF16 else 16
