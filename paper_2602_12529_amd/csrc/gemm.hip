@@ -23,8 +23,8 @@
 // the per-row / per-column dequantisation scales applied in the epilogue before
 // the bias.
 //
-// f32: a small-tile LDS FMA kernel with the same epilogues, for the float32
-// configurations.
+// f32: LDS FMA kernels with the same epilogues, for the float32 configurations: 32 x 32 tiles that split
+// K over their waves, and 64 x 64 tiles where there are many.
 #include <cmath>
 #include <type_traits>
 
@@ -979,13 +979,15 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_mid(GemmBatch batch) {
 }
 
 // ------------------------------------------------------------------ float32
-// 32 x 32 tiles of up to two problems (the streams of a dual block share the launch).  The float32
-// models are small and latency bound, so a tile's four waves each take a quarter of every 64-wide K
-// chunk (lane: a 4 x 4 block of outputs), the next chunk's loads are in flight meanwhile, and the
-// four partial sums meet in LDS at the end, added in wave order.  128 x 64 x 256 with the gated
-// epilogue: 24.7 us with 64 x 64 tiles walking K by 16; with these, and the text stream's 64 x 64 x 256
-// in the same launch, 9.6.
-constexpr int F32_T = 32, F32_K = 64, F32_LD = F32_T + 4;
+// 32 x 32 tiles (gemm_f32_kernel) or 64 x 64 ones (gemm_f32_wide_kernel) of up to two problems (the
+// streams of a dual block share the launch).
+//
+// 32 x 32, for launches of few tiles: the float32 models are small and latency bound, so a tile's four
+// waves each take a quarter of every 64-wide K chunk (lane: a 4 x 4 block of outputs), the next chunk's
+// loads are in flight meanwhile, and the four partial sums meet in LDS at the end, added in wave order.
+// 128 x 64 x 256 with the gated epilogue: 24.7 us with 64 x 64 tiles; with these, and the text stream's
+// 64 x 64 x 256 in the same launch, 9.6.
+constexpr int F32_T = 32, F32_K = 64, F32_LD = F32_T + 4, F32_WIDE = 64;
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmBatch batch) {
   __shared__ __attribute__((aligned(16))) float lds[2 * F32_K * F32_LD];
@@ -1068,6 +1070,58 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmBatch batch) {
         if (n0 + 4 * lc + e < p.N) epi_store<false, EPI>(p, m, n0 + 4 * lc + e, s[e]);
     }
   }
+}
+
+// 64 x 64, one problem a launch, where there are many tiles: those fill the CUs without a split of K, and
+// read each operand half as often.  K advances by 16 through LDS; a lane loads one element at a time, 16
+// lanes a row, so rows that do not start at 16 bytes cost nothing extra.  A workgroup per tile and the
+// problem as the kernel's own argument: walking tiles of a GemmBatch as the kernel above does cost 4 to 30%.
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_wide_kernel(GemmParams p) {
+  constexpr int T = F32_WIDE, TK = 16;
+  __shared__ float As[TK][T + 4];
+  __shared__ float Ws[TK][T + 4];
+  const int64_t m0 = static_cast<int64_t>(blockIdx.y) * T, n0 = static_cast<int64_t>(blockIdx.x) * T;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  float acc[4][4] = {};
+  const float* A1 = static_cast<const float*>(p.A1);
+  const float* A2 = static_cast<const float*>(p.A2);
+  const float* Wp = static_cast<const float*>(p.W);
+  for (int64_t k0 = 0; k0 < p.K; k0 += TK) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = threadIdx.x + i * 256;   // 0..1023 over [64 rows][16 k]
+      const int r = e >> 4, kk = e & 15;
+      const int64_t k = k0 + kk;
+      float av = 0.f, wv = 0.f;
+      if (k < p.K) {
+        const int64_t m = m0 + r, n = n0 + r;
+        if (m < p.M) av = k < p.K1 ? A1[m * p.lda1 + k] : A2[m * p.lda2 + (k - p.K1)];
+        if (n < p.N) wv = Wp[n * p.ldw + k];
+      }
+      As[kk][r] = av;
+      Ws[kk][r] = wv;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < TK; ++kk) {
+      float a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Ws[kk][tx * 4 + i]; }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
+      if (m < p.M && n < p.N) epi_store<false, EPI>(p, m, n, acc[i][j]);
+    }
 }
 
 // Compute units of the current device (one 256 x 256 tile runs per CU at a time).
@@ -1266,17 +1320,34 @@ int dispatch_bf16(const GemmParams& p0, const GemmParams* p1, hipStream_t s, dou
   return launch_pp_batch<EPI, 256>(b, s, kGemmNames[EPI], flops, bytes, ws, ws_bytes);
 }
 
+// From how many 32 x 32 tiles on a float32 problem takes 64 x 64 ones.  Measured, us, 32 x 32 and 64 x 64:
+//   rows of whole 16-byte pieces: 2048 x 1536 x 512 (3072 tiles) 61 and 67, x 3072 339 and 364; 2048 x 2048 x 512
+//   (4096) 80 and 77, x 3072 445 and 425; 4096 x 3072 x 3072 (12288) 1288 and 1116; 32 x 65536 x 3072 (2048)
+//   269 and 536.  A single chunk of K has no loads to hide: 2048 x 1024 x 64 (2048) 11.5 and 11.3, 2048 x 1536 x 64
+//   (3072) 15.2 and 13.7;
+//   other rows, which the small tiles load element by element: 1024 x 1024 x 333 (1024) 26 and 33, 2048 x 1024 x 333
+//   (2048) 45 and 36, 2048 x 2048 x 333 (4096) 87 and 53.
+bool f32_wide(const GemmParams& p) {
+  const int64_t from = !p.vec_k ? 2048 : p.K <= F32_K ? 3072 : 4096;
+  return tiles_of(p, F32_T, F32_T) >= from && (p.M + F32_WIDE - 1) / F32_WIDE <= 65535;   // the grid's second axis
+}
+
 // One float32 problem, or two with the same epilogue in one launch.
 template <int EPI>
 int dispatch_f32(const GemmParams& p0, const GemmParams* p1, hipStream_t s, double flops, double bytes) {
   static const char* names[3] = {"gemm_f32", "gemm_f32_gelu", "gemm_f32_gated"};
   constexpr int64_t max_blocks = 1 << 20;   // a workgroup walks on where there are more tiles
+  LaunchScope ls(names[EPI], s, flops, bytes);
+  if (!p1 && f32_wide(p0)) {
+    const dim3 grid(static_cast<unsigned>((p0.N + F32_WIDE - 1) / F32_WIDE), static_cast<unsigned>((p0.M + F32_WIDE - 1) / F32_WIDE));
+    hipLaunchKernelGGL(gemm_f32_wide_kernel<EPI>, grid, dim3(256), 0, s, p0);
+    return ls.status();
+  }
   GemmBatch b{};
   b.p[0] = p0;
   b.p[1] = p1 ? *p1 : p0;
   b.tiles0 = tiles_of(p0, F32_T, F32_T);
   b.tiles = b.tiles0 + (p1 ? tiles_of(*p1, F32_T, F32_T) : 0);
-  LaunchScope ls(names[EPI], s, flops, bytes);
   hipLaunchKernelGGL(gemm_f32_kernel<EPI>, dim3(static_cast<unsigned>(b.tiles < max_blocks ? b.tiles : max_blocks)),
                      dim3(256), 0, s, b);
   return ls.status();
@@ -1444,8 +1515,8 @@ int gemm2(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
   }
   const bool both = a0.dtype == a1.dtype && a0.epi == a1.epi && a0.M > 0 && a1.M > 0 && a0.N > 0 && a1.N > 0;
   const double flops = gemm_flops(a0) + gemm_flops(a1), bytes = gemm_bytes(a0) + gemm_bytes(a1);
-  if (both && a0.dtype == FF_F32) {
-    const GemmParams p0 = make_params(a0), p1 = make_params(a1);
+  const GemmParams p0 = make_params(a0), p1 = make_params(a1);
+  if (both && a0.dtype == FF_F32 && !f32_wide(p0) && !f32_wide(p1)) {
     switch (a0.epi) {
       case EPI_NONE: return dispatch_f32<EPI_NONE>(p0, &p1, s, flops, bytes);
       case EPI_GELU: return dispatch_f32<EPI_GELU>(p0, &p1, s, flops, bytes);
@@ -1457,7 +1528,6 @@ int gemm2(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
     FF_TRY(gemm(a0, s));
     return gemm(a1, s);
   }
-  const GemmParams p0 = make_params(a0), p1 = make_params(a1);
   switch (a0.epi) {
     case EPI_NONE: return dispatch_bf16<EPI_NONE>(p0, &p1, s, flops, bytes, a0.split_ws, a0.split_bytes);
     case EPI_GELU: return dispatch_bf16<EPI_GELU>(p0, &p1, s, flops, bytes, a0.split_ws, a0.split_bytes);

@@ -99,3 +99,18 @@ def normal(seed, shape, code=C.F32, scale=1.0):
 
 def say(*a):
     print(*a, flush=True)
+
+
+def best_us(fn, passes=20, repeats=5):
+    """Microseconds of a pass of fn among others, the best of a few repeats."""
+    fn()
+    best = math.inf
+    for _ in range(repeats):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(passes):
+            fn()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end) * 1e3 / passes)
+    return best

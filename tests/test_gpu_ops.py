@@ -13,7 +13,7 @@ from oracle import dit as odit
 from paper_2602_12529_amd import configs as C
 from paper_2602_12529_amd import synth
 
-from gpu_util import TOL, check, dev, host, normal, rel, say
+from gpu_util import TOL, best_us, check, dev, host, normal, rel, say
 
 pytestmark = pytest.mark.gpu
 
@@ -72,6 +72,22 @@ def test_linear_parity(gpu_lib, M, N, K, dt, epi):
 @pytest.mark.parametrize("epi", ["gelu_from", "gated"])
 def test_linear_f32_edges(gpu_lib, M, N, K, epi):
     test_linear_parity(gpu_lib, M, N, K, C.F32, epi)
+
+
+# float32 launches of many tiles: around 2048, 3072 (one chunk of K) and 4096 tiles of 32 x 32, ragged edges.
+@pytest.mark.parametrize("M,N,K", [(2000, 1030, 33), (1990, 1030, 33), (2040, 1532, 64), (2040, 2040, 68), (2000, 2040, 68)])
+@pytest.mark.parametrize("epi", ["gelu_from", "gated"])
+def test_linear_f32_many_tiles(gpu_lib, M, N, K, epi):
+    test_linear_parity(gpu_lib, M, N, K, C.F32, epi)
+
+
+def test_linear_f32_unaligned_rows_cost_no_more(gpu_lib):
+    """Many tiles: rows of 333 elements, which start at no 16 bytes, take as long as rows of 336."""
+    def us(K):
+        A, W, b = (torch.randn(s, device="cuda") for s in ((4097, K), (1001, K), (1001,)))
+        out = torch.empty((4097, 1001), device="cuda")
+        return best_us(lambda: gpu_lib.linear(A, W, b, out))
+    assert us(333) < 1.25 * us(336)
 
 
 # Grids that the smaller tiles take, each with 1, 2, 3, 5 and 7 slabs of 64 (fewer and more than the
