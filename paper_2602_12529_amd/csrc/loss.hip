@@ -274,12 +274,23 @@ int matching_loss(const char* fn, const void* a, const void* a2, const void* eps
   }
   {
     LaunchScope ls("loss_finalize", s, 0.0, static_cast<double>(B) * p.bps * 8.0 * (two ? 2.0 : 1.0));
-    // Up to 4096 samples one workgroup finishes everything (192 samples of 32 sums: 9.5 us in two launches,
-    // under 7 in one); more of them are spread over the CUs first.
-    if (B <= 4096) {
-      int W = 1;
-      while (W < 64 && W < p.bps) W *= 2;
-      while (W > 1 && B * W > 2 * kFinThreads) W /= 2;   // two steps over the samples, a lane's loads in flight together
+    // One workgroup finishes everything in one launch where its lanes walk few sums each; more of them are spread
+    // over the CUs first.  Whole passes, us, two launches and one (loads a lane makes: of both sums it waits for
+    // every pair, of one sum four are in flight):
+    //   up to 2048 sums: 32 samples of 64 (2 loads) 11.5 and 8.7, both sums 12.2 and 9.9; 1 of 2048 (32) 11.4 and 8.8,
+    //   both 12.0 and 22.5; 4 of 512 (8) both 12.0 and 11.8;
+    //   192 and more samples: 192 of 16 (4) 11.7 and 10.9, both 12.4 and 11.9; 192 of 32 (8) 17.6 and 17.0, both 18.3
+    //   and 20.5; 1000 of 16 (16) 34.2 and 34.9;
+    //   other sums: 8 of 512 (8) 14.2 and 12.8, both 14.7 and 17.4; 64 of 64 (4) 13.6 and 14.1, both 14.1 and 15.0; 1 of
+    //   8192 (128) 27.4 and 27.8, both 28 and 80.
+    int W = 1;
+    while (W < 64 && W < p.bps) W *= 2;
+    while (W > 1 && B * W > 2 * kFinThreads) W /= 2;
+    const int64_t loads = (B * W + kFinThreads - 1) / kFinThreads * ((p.bps + W - 1) / W);
+    const bool one = B * p.bps <= 2048 ? loads <= (two ? 8 : 32)
+                     : B >= 192        ? B <= 4096 && loads <= (two ? 4 : 8)
+                                       : !two && B <= 16 && loads <= 32;
+    if (one) {
       if (two) hipLaunchKernelGGL(loss_mean_kernel<true>, dim3(1), dim3(kFinThreads), 0, s, partial, B, p.bps, W, w, per, loss);
       else hipLaunchKernelGGL(loss_mean_kernel<false>, dim3(1), dim3(kFinThreads), 0, s, partial, B, p.bps, W, w, per, loss);
       return ls.status();

@@ -18,7 +18,7 @@ import torch
 from oracle import losses as OL
 from paper_2602_12529_amd import configs as C
 
-from gpu_util import TOL, dev, host, normal, rel, say
+from gpu_util import TOL, best_us, dev, host, normal, rel, say
 
 pytestmark = pytest.mark.gpu
 
@@ -70,6 +70,44 @@ def test_awm_and_nft_loss_parity(gpu_lib, dt, B, D):
 @pytest.mark.parametrize("B,D", [(1, 200000), (3, 30000), (300, 2056), (4096, 8), (4097, 8)])
 def test_matching_loss_sample_counts(gpu_lib, B, D):
     test_awm_and_nft_loss_parity(gpu_lib, C.F32, B, D)
+
+
+# Of few partial sums (of 2048 elements) a lane one workgroup finishes everything, of more two launches; the first of
+# each pair is the last that NFT or AWM finishes in one.
+@pytest.mark.parametrize("B,sums", [(192, 16), (192, 17), (192, 32), (192, 33), (32, 64), (33, 63), (16, 512), (17, 482)])
+def test_matching_loss_partial_sums(gpu_lib, B, sums):
+    say("awm/nft", B, sums)
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    v, vn, eps, x0 = (torch.randn((B, sums * 2048 - 8), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(4))
+    adv, r = torch.randn(B, device="cuda", generator=gen), torch.linspace(0, 1, B, device="cuda")
+    per, loss = gpu_lib.awm_loss(v, eps, x0, adv)
+    per2, loss2 = gpu_lib.nft_loss(v, vn, eps, x0, r)
+    target = eps.double() - x0.double()
+    s1, s2 = (((a.double() - target) ** 2).sum(-1) for a in (v, vn))
+    ref, ref2 = adv.double() * s1, r.double() * s1 + (1 - r.double()) * s2
+    np.testing.assert_allclose(host(per), host(ref), rtol=LOSS_REL)
+    np.testing.assert_allclose(host(per2), host(ref2), rtol=LOSS_REL)
+    assert loss.item() == pytest.approx(ref.mean().item(), rel=LOSS_REL, abs=LOSS_REL * ref.abs().mean().item())
+    assert loss2.item() == pytest.approx(ref2.mean().item(), rel=LOSS_REL)
+
+
+def test_matching_loss_of_one_long_sample(gpu_lib):
+    """One sample of 16384 partial sums: the sums against float64, and NFT, which reads four tensors where AWM
+    reads three (4/3 of the traffic), takes no more than 1.6 times as long."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    v, vn, eps, x0 = (torch.randn((1, 1 << 26), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(4))
+    adv, r = torch.tensor([0.7], device="cuda"), torch.tensor([0.25], device="cuda")
+    per, loss = gpu_lib.awm_loss(v, eps, x0, adv)
+    per2, loss2 = gpu_lib.nft_loss(v, vn, eps, x0, r)
+    target = eps.double() - x0.double()
+    s1, s2 = (((a.double() - target) ** 2).sum().item() for a in (v, vn))
+    assert per.item() == pytest.approx(float(adv[0]) * s1, rel=LOSS_REL) and loss.item() == per.item()
+    assert per2.item() == pytest.approx(0.25 * s1 + 0.75 * s2, rel=LOSS_REL) and loss2.item() == per2.item()
+    ws = torch.empty(gpu_lib.loss_workspace_size(1, 1 << 26), dtype=torch.uint8, device="cuda")
+    awm = best_us(lambda: gpu_lib.awm_loss(v, eps, x0, adv, per, loss, ws))
+    nft = best_us(lambda: gpu_lib.nft_loss(v, vn, eps, x0, r, per2, loss2, ws))
+    say(f"one long sample: AWM {awm:.1f} us, NFT {nft:.1f} us")
+    assert nft < 1.6 * awm
 
 
 def test_awm_loss_of_the_exact_velocity_is_zero(gpu_lib):
