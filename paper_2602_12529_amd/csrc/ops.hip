@@ -308,20 +308,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void s
 // per lane (row width 512 * NCH, 16-byte aligned) and a wave walks ROWS rows,
 // keeping the sample's (1 + scale) and shift for its columns in registers
 // (reloaded only when the sample changes), so every global access is a
-// 16-byte vector access.  NCH == 0: generic scalar path, one row per wave.
+// 16-byte vector access.  NCH == 0: generic scalar path, one row per wave; NCH < 0: and a
+// wave walks rows, from 2^26 of them on, for a launch takes fewer than 2^32 threads (the walk costs
+// launches that do not need it up to 5%).
 constexpr int kNormRows = 4;
 
-// Up to two problems in one launch: workgroups [0, blocks0) belong to a[0].
+// Two problems in one launch: workgroups [0, blocks0) belong to a[0].
 struct NormPair {
   NormArgs a[2];
   unsigned blocks0;
 };
 
-template <bool BF16, int NCH>
-__global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
+// A launch's arguments (one problem or two) as a workgroup sees them.  A single problem is the kernel's own
+// argument: looked up in a pair, its loads wait for one another (one row of 1536 float32: 0.4 us of 9.7;
+// 32768 rows of 100: 2 of 11).
+__device__ __forceinline__ const NormArgs& norm_problem(const NormArgs& one, int64_t& block, int64_t& blocks) {
+  block = blockIdx.x;
+  blocks = gridDim.x;
+  return one;
+}
+__device__ __forceinline__ const NormArgs& norm_problem(const NormPair& pair, int64_t& block, int64_t& blocks) {
   const bool first = blockIdx.x < pair.blocks0;
-  const NormArgs& a = pair.a[first ? 0 : 1];
-  const int64_t block = first ? blockIdx.x : blockIdx.x - pair.blocks0;
+  block = first ? blockIdx.x : blockIdx.x - pair.blocks0;
+  blocks = first ? pair.blocks0 : gridDim.x - pair.blocks0;
+  return pair.a[first ? 0 : 1];
+}
+
+template <bool BF16, int NCH, typename Args>
+__global__ __launch_bounds__(256) void norm_kernel(Args args) {
+  int64_t block, blocks;
+  const NormArgs& a = norm_problem(args, block, blocks);
   const int lane = threadIdx.x & 63;
   const int64_t H = a.H;
   const float invH = 1.0f / static_cast<float>(H);
@@ -389,9 +405,7 @@ __global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
       }
     }
   } else {
-    // A launch takes fewer than 2^32 threads, so from 2^26 rows on a wave walks several.
-    const int64_t stride = 4 * static_cast<int64_t>(first ? pair.blocks0 : gridDim.x - pair.blocks0);
-    for (int64_t row = block * 4 + (threadIdx.x >> 6); row < a.rows; row += stride) {
+    auto one_row = [&](int64_t row) {
       const int64_t b = row / a.rows_per_sample;
       const float* sh = a.shift ? a.shift + b * a.mod_ld : nullptr;
       const float* sc = a.scale ? a.scale + b * a.mod_ld : nullptr;
@@ -416,6 +430,12 @@ __global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
       const float rstd = rsqrtf(wave_sum(ss) * invH + a.eps);
       for (int64_t j = lane; j < H; j += 64)
         st1<BF16>(a.y, row * a.ldy + j, finish(j, (ld1<BF16>(a.x, row * a.ldx + j) - mean) * rstd));
+    };
+    const int64_t row0 = block * 4 + (threadIdx.x >> 6);
+    if constexpr (NCH == 0) {
+      if (row0 < a.rows) one_row(row0);
+    } else {
+      for (int64_t row = row0; row < a.rows; row += 4 * blocks) one_row(row);
     }
   }
 }
@@ -427,11 +447,10 @@ __global__ __launch_bounds__(256) void norm_kernel(NormPair pair) {
 // not again until its cached copy would long be gone): 11% faster on 32768 x 3072 rows read from
 // HBM, within noise in the rollout, where the previous GEMM has just written them; non-temporal
 // stores as well were slower.
-template <int NCH, int RPW>
-__global__ __launch_bounds__(256) void norm_lds_kernel(NormPair pair) {
-  const bool first = blockIdx.x < pair.blocks0;
-  const NormArgs& a = pair.a[first ? 0 : 1];
-  const int64_t block = first ? blockIdx.x : blockIdx.x - pair.blocks0;
+template <int NCH, int RPW, typename Args>
+__global__ __launch_bounds__(256) void norm_lds_kernel(Args args) {
+  int64_t block, blocks;
+  const NormArgs& a = norm_problem(args, block, blocks);
   extern __shared__ __attribute__((aligned(16))) float mod_s[];   // [2][H]: mul, add
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t H = a.H;
@@ -504,7 +523,7 @@ __global__ __launch_bounds__(256) void norm_lds_kernel(NormPair pair) {
 
 // How a launch of one problem, or of two of the same width (the streams of a dual block), runs.
 struct NormPlan {
-  int nch;          // 16-byte chunks a lane holds of a row; 0: the element-wise path
+  int nch;          // 16-byte chunks a lane holds of a row; 0: the element-wise path, -1: and a wave walks rows
   int block_rows;   // rows per workgroup of norm_lds_kernel; 0: norm_kernel
 };
 constexpr int64_t kNormMaxBlocks = (int64_t(1) << 24) - 1;   // 256 threads each: a launch takes fewer than 2^32
@@ -532,33 +551,29 @@ NormPlan norm_plan(const NormArgs* a, int n) {
       if (a[i].rows_per_sample % per != 0 && a[i].rows > a[i].rows_per_sample) return false;
     return true;
   };
+  // Where the samples' lengths allow only smaller blocks than the row count asks for, norm_kernel's 16 rows
+  // a workgroup of any samples are faster, except for
+  //   - up to 20 x 512 rows (10 samples of 1020 rows, us, norm_kernel and 4 rows: H = 512 7.9 and 6.4, 1024 10.6 and
+  //     9.3, 3072 31.4 and 24.2; 16 samples: 8.2 and 8.5, 13.0 and 14.0, 38.5 and 41.0);
+  //   - H = 3072, where norm_kernel's modulation vectors take the registers of half its waves (24 of 1032, 8 rows:
+  //     71 and 61);
+  //   - more rows than the last-level cache keeps (64 of 1032, 8 rows: H = 1536 86 and 66; 24 of 1028, 4 rows:
+  //     27 and 32; 64 of 1028, H = 512, 4 rows: 24 and 33).
   const int want = rows >= 64 * 512 ? 64 : rows >= 32 * 512 ? 32 : rows >= 8 * 512 ? 8 : 4;
   for (int per : {want, 8, 4})
     if (per <= want && usable(per)) {
-      p.block_rows = per;
+      if (per == want || rows <= 20 * 512 || (want > 8 && p.nch == 6) || rows * a[0].H >= int64_t(80) << 20) p.block_rows = per;
       break;
     }
   return p;
 }
 
-template <bool BF16>
-int norm_launch(const NormPlan& p, const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
-  NormPair pr{};
-  pr.a[0] = a0;
-  pr.a[1] = a1 ? *a1 : a0;
-  auto blocks = [&](const NormArgs& a, int64_t per) {
-    const int64_t b = (a.rows + per - 1) / per, most = a1 ? kNormMaxBlocks / 2 : kNormMaxBlocks;
-    return static_cast<unsigned>(b < most ? b : most);   // reached on the element-wise path only, which strides
-  };
-  auto grid_of = [&](int64_t per) {
-    pr.blocks0 = blocks(a0, per);
-    return dim3(pr.blocks0 + (a1 ? blocks(*a1, per) : 0u));
-  };
+template <bool BF16, typename Args>
+void norm_launch(const NormPlan& p, unsigned blocks, int64_t H, const Args& args, hipStream_t s) {
   if (p.block_rows > 0) {
-    const dim3 grid = grid_of(p.block_rows);
-    const size_t shm = 2 * a0.H * sizeof(float);
+    const size_t shm = 2 * H * sizeof(float);
     switch (p.nch * 100 + p.block_rows) {
-#define FF_NL(N, R) case N * 100 + R: hipLaunchKernelGGL((norm_lds_kernel<N, R / 4>), grid, dim3(256), shm, s, pr); return FF_OK;
+#define FF_NL(N, R) case N * 100 + R: hipLaunchKernelGGL((norm_lds_kernel<N, R / 4, Args>), dim3(blocks), dim3(256), shm, s, args); return;
       FF_NL(1, 32) FF_NL(2, 32) FF_NL(3, 32) FF_NL(4, 32) FF_NL(5, 32) FF_NL(6, 32)
       FF_NL(1, 4) FF_NL(2, 4) FF_NL(3, 4) FF_NL(4, 4) FF_NL(5, 4) FF_NL(6, 4)
       FF_NL(1, 8) FF_NL(2, 8) FF_NL(3, 8) FF_NL(4, 8) FF_NL(5, 8) FF_NL(6, 8)
@@ -566,14 +581,28 @@ int norm_launch(const NormPlan& p, const NormArgs& a0, const NormArgs* a1, hipSt
 #undef FF_NL
     }
   }
-  const dim3 grid = grid_of(p.nch > 0 ? 4 * kNormRows : 4);
   switch (p.nch) {
-#define FF_NM(N) case N: hipLaunchKernelGGL((norm_kernel<BF16, N>), grid, dim3(256), 0, s, pr); break;
-    FF_NM(1) FF_NM(2) FF_NM(3) FF_NM(4) FF_NM(5) FF_NM(6) FF_NM(7) FF_NM(8)
+#define FF_NM(N) case N: hipLaunchKernelGGL((norm_kernel<BF16, N, Args>), dim3(blocks), dim3(256), 0, s, args); break;
+    FF_NM(1) FF_NM(2) FF_NM(3) FF_NM(4) FF_NM(5) FF_NM(6) FF_NM(7) FF_NM(8) FF_NM(-1)
 #undef FF_NM
-    default: hipLaunchKernelGGL((norm_kernel<BF16, 0>), grid, dim3(256), 0, s, pr); break;
+    default: hipLaunchKernelGGL((norm_kernel<BF16, 0, Args>), dim3(blocks), dim3(256), 0, s, args); break;
   }
-  return FF_OK;
+}
+
+template <bool BF16>
+void norm_dispatch(const NormArgs& a0, const NormArgs* a1, hipStream_t s) {
+  const NormArgs a[2] = {a0, a1 ? *a1 : a0};
+  NormPlan p = norm_plan<BF16>(a, a1 ? 2 : 1);
+  const int64_t per = p.block_rows > 0 ? p.block_rows : p.nch > 0 ? 4 * kNormRows : 4;
+  auto blocks = [&](const NormArgs& x) {
+    const int64_t b = (x.rows + per - 1) / per, most = a1 ? kNormMaxBlocks / 2 : kNormMaxBlocks;
+    if (b <= most) return static_cast<unsigned>(b);
+    p.nch = -1;   // reached by the element-wise path only
+    return static_cast<unsigned>(most);
+  };
+  const unsigned blocks0 = blocks(a0), blocks1 = a1 ? blocks(*a1) : 0u;
+  if (!a1) return norm_launch<BF16>(p, blocks0, a0.H, a0, s);
+  norm_launch<BF16>(p, blocks0 + blocks1, a0.H, NormPair{{a0, *a1}, blocks0}, s);
 }
 
 // ------------------------------------------------------------------ QK norm + RoPE + relayout
@@ -919,22 +948,10 @@ int quantize_fp8(int dtype, const void* x, int64_t ldx, void* q, int64_t ldq, fl
   return ls.status();
 }
 
-namespace {
-template <bool BF16>
-int norm_one(const NormArgs& a, hipStream_t s) {
-  return norm_launch<BF16>(norm_plan<BF16>(&a, 1), a, nullptr, s);
-}
-template <bool BF16>
-int norm_two(const NormArgs& a0, const NormArgs& a1, hipStream_t s) {
-  const NormArgs a[2] = {a0, a1};
-  return norm_launch<BF16>(norm_plan<BF16>(a, 2), a0, &a1, s);
-}
-}  // namespace
-
 int norm_modulate(const NormArgs& a, hipStream_t s) {
   if (a.rows == 0) return FF_OK;
   LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a.dtype) * a.rows * a.H);
-  FF_TRY(a.dtype == FF_BF16 ? norm_one<true>(a, s) : norm_one<false>(a, s));
+  a.dtype == FF_BF16 ? norm_dispatch<true>(a, nullptr, s) : norm_dispatch<false>(a, nullptr, s);
   return ls.status();
 }
 
@@ -945,7 +962,7 @@ int norm_modulate2(const NormArgs& a0, const NormArgs& a1, hipStream_t s) {
     return norm_modulate(a1, s);
   }
   LaunchScope ls("norm_modulate", s, 0.0, 2.0 * dtype_size(a0.dtype) * (a0.rows + a1.rows) * a0.H);
-  FF_TRY(a0.dtype == FF_BF16 ? norm_two<true>(a0, a1, s) : norm_two<false>(a0, a1, s));
+  a0.dtype == FF_BF16 ? norm_dispatch<true>(a0, &a1, s) : norm_dispatch<false>(a0, &a1, s);
   return ls.status();
 }
 

@@ -325,6 +325,30 @@ def test_norm_modulate_few_rows(gpu_lib, rows, rps):
     test_norm_modulate_staged_path(gpu_lib, rows, rps)
 
 
+# From 4096 rows on, samples whose length is no multiple of the block's rows: 4-row blocks up to 10240 rows, then
+# 16 rows of any samples, from 80 x 2^20 elements on 8-row or 4-row blocks again; 3072 columns keep the small
+# blocks from 16384 rows.
+@pytest.mark.parametrize("H,n,rps", [(512, 10, 1020), (512, 11, 1020), (1536, 32, 1028), (3072, 17, 1028), (1536, 56, 1032), (2560, 34, 1028)])
+def test_norm_modulate_odd_samples(gpu_lib, H, n, rps):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    draw = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    x, mod = draw(n * rps, H).to(torch.bfloat16), draw(n, 2 * H)
+    y = torch.empty_like(x)
+    gpu_lib.norm_modulate(x, y, shift=mod, scale=mod[:, H:], mod_ld=2 * H, rows_per_sample=rps)
+    xd = x.double().view(n, rps, H)
+    ref = xd * torch.rsqrt(xd.square().mean(-1, keepdim=True) + 1e-6) * (1 + mod[:, None, H:].double()) + mod[:, None, :H].double()
+    check(host(y), host(ref.view(-1, H)), C.BF16, 0, H, what=f"norm_modulate {n} x {rps} x {H}", norm_tol=6e-3)
+
+
+def test_norm_modulate_sample_length_costs_no_more(gpu_lib):
+    """64 samples of 1044 rows (a multiple of 4) take no longer than 64 of 1046, which no block size divides."""
+    def us(rps):
+        x, mod = torch.randn((64 * rps, 512), device="cuda").to(torch.bfloat16), torch.randn((64, 1024), device="cuda")
+        y = torch.empty_like(x)
+        return best_us(lambda: gpu_lib.norm_modulate(x, y, shift=mod, scale=mod[:, 512:], mod_ld=1024, rows_per_sample=rps))
+    assert us(1044) < 1.15 * us(1046)
+
+
 # A launch takes fewer than 2^32 threads: 4 rows (or tokens) a workgroup of 256 end at 2^26 of them.
 @pytest.mark.parametrize("H,rps,dt", [(512, 12, C.BF16), (8, 12, C.F32)])
 def test_norm_modulate_many_rows(gpu_lib, H, rps, dt):
