@@ -103,15 +103,33 @@ def test_linear_tile_choice(gpu_lib, M, N, slabs, epi):
     test_linear_parity(gpu_lib, M, N, 64 * slabs, C.BF16, epi)
 
 
-# 256 x 256 tiles leaving a partly filled last round on 256 CUs, K of at least 96 slabs of 64:
-# (17 x 16 = 272 tiles, tail 16, split in 8), (17 x 17 = 289, tail 33, split in 7), (33 x 9 = 297
-# with ragged edges, tail 41, split in 6); 192 x 256 tiles: (32 x 12 = 384, tail 128, split in 2).
-LIN_SPLIT = [(4352, 4096, 6144), (4352, 4352, 12288), (8200, 2100, 6144), (6140, 3072, 12288)]
+# Launches that leave a partly filled last round on 256 CUs, K of at least 96 slabs of 64: M, N, K, and the tile's
+# rows, the tiles of the last round and the parts each is split in (288 = 18 x 16 tiles of 256 x 256, 289 = 17 x 17,
+# 297 = 33 x 9 with ragged edges; 368 = 23 x 16 of 192 x 256, 384 = 32 x 12, 338 = 26 x 13).
+LIN_SPLIT = [(4352, 4096, 6144, 192, 112, 2), (4352, 4352, 12288, 256, 33, 7), (8200, 2100, 6144, 256, 41, 6),
+             (6140, 3072, 12288, 192, 128, 2), (4092, 4608, 6144, 256, 32, 8), (4924, 3328, 6144, 192, 82, 3)]
+UNWRITTEN = 0xA5
 
 
-@pytest.mark.parametrize("M,N,K", LIN_SPLIT)
+def split_workspace(gpu_lib):
+    return torch.full((gpu_lib.linear_workspace_size(),), UNWRITTEN, dtype=torch.uint8, device="cuda")
+
+
+def check_split_workspace(ws, rows, tail, parts):
+    """What a launch leaves in a workspace filled with UNWRITTEN: a cleared flag of 8 bytes for each of the tail's
+    tail x (parts - 1) partial sums, and from the next multiple of 256 on those sums, rows x 256 floats each."""
+    blocks = tail * (parts - 1)
+    first = (8 * blocks + 255) // 256 * 256
+    assert not ws[:8 * blocks].any(), "a flag was left set"
+    assert (ws[8 * blocks:first] == UNWRITTEN).all()
+    written = (ws[first:] != UNWRITTEN).nonzero()
+    end = first + blocks * rows * 256 * 4
+    assert end - 64 < first + int(written[-1]) + 1 <= end, (first, int(written[-1]), end)
+
+
+@pytest.mark.parametrize("M,N,K,rows,tail,parts", LIN_SPLIT)
 @pytest.mark.parametrize("epi", ["bias", "gelu", "gated"])
-def test_linear_split_k_tail(gpu_lib, M, N, K, epi):
+def test_linear_split_k_tail(gpu_lib, M, N, K, rows, tail, parts, epi):
     """With a workspace the last round's tiles are split along K and their float32 partial sums added
     in a fixed order: the result matches the oracle element-wise, repeats bit for bit, and differs
     (in rounding only) from the unsplit launch, which shows the split path ran."""
@@ -133,29 +151,34 @@ def test_linear_split_k_tail(gpu_lib, M, N, K, epi):
         ref, code = resid + gate[np.arange(M) // rps] * z, gpu_lib.EPI_GATED
     else:
         ref = z
-    ws = torch.empty(gpu_lib.linear_workspace_size(), dtype=torch.uint8, device="cuda")
+    ws = split_workspace(gpu_lib)
     outs = []
     for use_ws in (True, True, False):
         out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
         gpu_lib.linear(A, W, Bv, out, epi=code, ws=ws if use_ws else None, **kw)
         outs.append(out)
     torch.cuda.synchronize()
+    check_split_workspace(ws, rows, tail, parts)
     check(host(outs[0]), ref, C.BF16, 0, K, what=f"linear split-K {M}x{N}x{K} {epi}", norm_tol=6e-3)
     assert torch.equal(outs[0], outs[1])
     assert not torch.equal(outs[0], outs[2])
     check(host(outs[2]), ref, C.BF16, 0, K, what=f"linear unsplit {M}x{N}x{K} {epi}", norm_tol=6e-3)
 
 
-@pytest.mark.parametrize("M,N,K", [(4352, 4096, 6144), (6140, 3072, 12288)])
-def test_linear_split_k_graph_replays(gpu_lib, M, N, K):
-    """A captured launch whose last round is split along K: every replay, on new inputs and with eager
-    launches of the same kernel on the same workspace in between, equals the eager result bit for bit."""
-    say("linear split-K graph", M, N, K)
+# One and several partial sums a tile, of 192 and of 256 rows.
+@pytest.mark.parametrize("M,N,K,rows,tail,parts", [LIN_SPLIT[i] for i in (0, 1, 3, 5)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_linear_split_k_graph_replays(gpu_lib, M, N, K, rows, tail, parts, shared):
+    """A captured launch whose last round is split along K: every replay, on new inputs, equals the eager result
+    bit for bit and leaves its flags cleared, with the eager launches on a workspace of their own (nothing else
+    touches the replays' flags) or on the same one."""
+    say("linear split-K graph", M, N, K, shared)
     gen = torch.Generator(device="cuda").manual_seed(M)
     draw = lambda *s: torch.randn(s, device="cuda", generator=gen).to(torch.bfloat16)
     A, W, b = draw(M, K), draw(N, K) * 0.02, draw(N)
     out, ref = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2))
-    ws = torch.empty(gpu_lib.linear_workspace_size(), dtype=torch.uint8, device="cuda")
+    ws = split_workspace(gpu_lib)
+    ref_ws = ws if shared else split_workspace(gpu_lib)
     gpu_lib.linear(A, W, b, out, ws=ws)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
@@ -165,7 +188,8 @@ def test_linear_split_k_graph_replays(gpu_lib, M, N, K):
         A.copy_(draw(M, K))
         graph.replay()
         torch.cuda.synchronize()
-        gpu_lib.linear(A, W, b, ref, ws=ws)
+        check_split_workspace(ws, rows, tail, parts)
+        gpu_lib.linear(A, W, b, ref, ws=ref_ws)
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
 
