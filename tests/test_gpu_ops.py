@@ -194,6 +194,27 @@ def test_linear_split_k_graph_replays(gpu_lib, M, N, K, rows, tail, parts, share
         assert torch.equal(out, ref)
 
 
+def test_bf16_rounding_of_every_float32(gpu_lib):
+    """The epilogues' conversion, over all 2^32 floats: a gated product of 1 on a residual of -0 stores the float32
+    gate rounded to bf16. To nearest, ties to even, signed zeros, subnormals and infinities kept, NaN stays NaN."""
+    M, N, K = 65536, 4096, 64
+    A, W = torch.zeros((M, K), device="cuda", dtype=torch.bfloat16), torch.zeros((N, K), device="cuda", dtype=torch.bfloat16)
+    A[:, 0] = W[:, 0] = 1.0
+    resid = torch.full((M, N), -0.0, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty_like(resid)
+    for part in range(16):
+        first = part * M * N - (1 << 31)
+        bits = torch.arange(first, first + M * N, device="cuda", dtype=torch.int64)
+        gate = bits.to(torch.int32).view(torch.float32).view(M, N)
+        gpu_lib.linear(A, W, None, out, epi=gpu_lib.EPI_GATED, gate=gate, gate_ld=N, resid=resid, rows_per_sample=1)
+        bits &= 0xFFFFFFFF
+        want = ((bits + 0x7FFF + ((bits >> 16) & 1)) >> 16).to(torch.int16).view(M, N)
+        del bits
+        nan = torch.isnan(gate)
+        assert torch.equal(torch.isnan(out), nan)
+        assert bool(((out.view(torch.int16) == want) | nan).all()), part
+
+
 def test_linear_in_place_gated_residual(gpu_lib):
     M, N, K = 256, 384, 128
     a, w = normal(6, (M, K), C.BF16), normal(7, (N, K), C.BF16, 0.05)
