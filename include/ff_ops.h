@@ -32,9 +32,10 @@ enum { FF_EPI_BIAS = 0, FF_EPI_GELU = 1, FF_EPI_GATED = 2 };
  * (FF_EUNSUPPORTED): M, N <= 2^27; K and the row strides <= 2^22 elements; at most 2^31 - 1
  * tiles of 128 x 128.
  * workspace (device, 16-byte aligned, ff_linear_workspace_size bytes) or NULL: with it, a bf16
- * launch whose 256 x 256 tiles leave a last, partly filled round of the GPU's compute units splits
- * that round's tiles along K (float32 partial sums in the workspace, added in a fixed order, so the
- * result is deterministic); without it nothing is split.  The workspace holds nothing between
+ * launch of long K whose 256 x 256 or 192 x 256 tiles leave a last, partly filled round of the GPU's
+ * compute units splits that round's tiles along K (float32 partial sums in the workspace, added in a
+ * fixed order, so the result is deterministic), and the choice of the tile counts on it; without it
+ * nothing is split and another tile may be chosen.  The workspace holds nothing between
  * calls; calls that overlap on one workspace race. */
 int ff_linear(const void* A, int64_t lda, const void* W, const void* bias, void* out, int64_t ldo,
               int64_t M, int64_t N, int64_t K, int32_t epi, int64_t gelu_from, const float* gate,

@@ -114,7 +114,7 @@ struct GemmBatch {
   int64_t tiles0, tiles;
   int64_t split_from;
   int parts;
-  float4* partial;           // [split tiles][parts - 1][32 float4][512 threads]
+  float4* partial;           // [split tiles][parts - 1][32 float4 (192 tile rows: 24)][512 threads]
   uint64_t* flags;           // [split tiles][parts - 1]
   uint64_t epoch;
 };
@@ -475,7 +475,7 @@ __device__ __forceinline__ void wg_barrier() {
 // ------------------------------------------------------------------ bf16, 256 x 256, ping-pong
 // Eight waves, two per SIMD, in two groups of four (wave w and wave w + 4 share a SIMD).
 // Each wave owns a 128 x 64 block of the 256 x 256 tile (4 x 2 MFMA blocks) and alternates
-// between a compute phase (the 32 MFMAs of one 64-wide K slab) and a memory phase (the LDS
+// between a compute phase (the 32 MFMAs of one 64-wide K slab, 24 with 192 tile rows) and a memory phase (the LDS
 // reads of the fragments it needs next); the groups are one phase apart, so one wave of a
 // SIMD keeps the matrix core busy while the other feeds itself.  A barrier separates
 // phases: slab s is computed by group 0 in phase 2s and by group 1 in phase 2s + 1, so it
@@ -652,7 +652,7 @@ __device__ __forceinline__ void pp_body(const GemmBatch& batch) {
       }
     }
   };
-  // The MFMAs of a slab (32 bf16 or 16 fp8); with `rb` set, the eight W-row loads of a later
+  // The MFMAs of a slab (32 bf16, 24 with 192 tile rows, or 16 fp8); with `rb` set, the eight W-row loads of a later
   // slab go out one after each of the first eight MFMAs: the loads must land by the end of the
   // next phase, and issuing them early in this one gives them most of two phases to arrive
   // (spread evenly over the phase, the last one had little more than one).
@@ -1228,8 +1228,15 @@ double tile_us(const TileKind& k, const GemmParams& p0, const GemmParams* p1, in
 TileKind choose_tile(const GemmParams& p0, const GemmParams* p1, int cus, bool split_ws, double* us) {
   const TileKind* best = &kTileKinds[0];
   *us = tile_us(*best, p0, p1, cus, split_ws);
-  // Where the 256 x 256 launch's last round can be split, only tiles whose launch can be are compared:
-  // with K that long the smaller ones lose (6144 x 3072 x 12288: 395 and 434 us split, 429 and 463 not).
+  // Where the 256 x 256 launch's last round can be split, only tiles whose launch can be are compared, for the
+  // expected times of split and unsplit launches are not fitted closely enough to be compared with each other.
+  // Gated, us, so chosen and the choice among unsplit launches, at K = 6144, 8192 and 12288:
+  //   4097 x 4096 (272 tiles of 256 x 256)  188 and 215, 237 and 273, 343 and 406
+  //   5120 x 4096 (320)                     250 and 229, 311 and 296, 441 and 477
+  //   6144 x 4096 (384)                     261 and 245, 332 and 319, 487 and 524
+  //   12288 x 3072 (576)                    413 and 369, 518 and 501, 760 and 763
+  // So it pays from K = 12288 on and costs some shapes up to 12% below; before there were smaller tiles to choose,
+  // these launches took 254, 265, 276 and 434 at K = 6144.
   const bool split_only = split_ws && splits(*best, p0, p1, cus);
   for (const TileKind& k : kTileKinds) {
     if (split_only && !splits(k, p0, p1, cus)) continue;

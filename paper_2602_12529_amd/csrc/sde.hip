@@ -499,7 +499,7 @@ namespace {
 
 constexpr int kAdvThreads = 256;
 constexpr int kAdvMaxK = 16;
-constexpr int kAdvMaxStats = 4096;
+constexpr int kAdvMaxStats = 4096;   // n_groups * K: the interface's limit; no buffer of the kernel is sized by it
 
 // Value j of sample i: the weighted reward sum (mode 0, j = 0) or reward j (mode 1).
 __device__ __forceinline__ double adv_value(const float* r, const float* w, int64_t i, int K, int mode, int j) {
