@@ -1197,11 +1197,11 @@ int64_t tiles256(const GemmParams& p) { return tiles_of(p, 256, 256); }
 // CUs, each its slabs and what a round costs besides (first loads, epilogue).  The constants (us on 256
 // CUs) are fits to the gated epilogue at K = 1536 .. 15360; a slab takes less when part of the CUs idle,
 // for the clock is higher then.  Measured, us, the chosen one first:
-//   1536 x 3072 x 12288: 128 x 192 121 (one round of 192), 128 x 256 136, 192 x 256 180, 256 x 256 218
-//   4608 x 3072 x 3072:  256 x 256 79 (one round of 216), 128 x 256 90, 128 x 192 112
-//   4000 x 3072 x 15360: 192 x 256 296 (one round of 252), 256 x 256 319 (of 192), 128 x 192 354
-//   6144 x 3072 x 12288: 192 x 256 395 (1.5 rounds, the half one split along K), 256 x 256 434 (1.125)
-//   36864 x 3072 x 12288: 256 x 256 2168, 192 x 256 2280 (more loads per product), 128 x 256 2538
+//   1536 x 3072 x 12288: 128 x 192 120 (one round of 192), 128 x 256 130, 192 x 256 181, 256 x 256 211
+//   4608 x 3072 x 3072:  256 x 256 80 (one round of 216), 128 x 256 92, 128 x 192 115
+//   4000 x 3072 x 15360: 192 x 256 290 (one round of 252), 256 x 256 313 (of 192), 128 x 192 350
+//   6144 x 3072 x 12288: 192 x 256 388 (1.5 rounds, the half one split along K), 256 x 256 430 (1.125)
+//   36864 x 3072 x 12288: 256 x 256 2167, 192 x 256 2272 (more loads per product), 128 x 256 2538
 struct TileKind {
   int bm, bn;
   double slab, round;
