@@ -546,7 +546,7 @@ NormPlan norm_plan(const NormArgs* a, int n) {
   // Rows per workgroup, all of one sample: few rows are spread over the CUs, one a wave (512 + 1024 rows
   // of 3072: 21 us in two launches of two rows a wave, 8.7 us in this one).
   auto usable = [&](int64_t per) {
-    if (rows / per + n > kNormMaxBlocks) return false;
+    if (rows / per + n > kNormMaxBlocks / n) return false;   // a pair's problems take half of the grid each
     for (int i = 0; i < n; ++i)
       if (a[i].rows_per_sample % per != 0 && a[i].rows > a[i].rows_per_sample) return false;
     return true;
@@ -557,8 +557,8 @@ NormPlan norm_plan(const NormArgs* a, int n) {
   //     9.3, 3072 31.4 and 24.2; 16 samples: 8.2 and 8.5, 13.0 and 14.0, 38.5 and 41.0);
   //   - H = 3072, where norm_kernel's modulation vectors take the registers of half its waves (24 of 1032, 8 rows:
   //     71 and 61);
-  //   - more rows than the last-level cache keeps (64 of 1032, 8 rows: H = 1536 86 and 66; 24 of 1028, 4 rows:
-  //     27 and 32; 64 of 1028, H = 512, 4 rows: 24 and 33).
+  //   - more elements than the last-level cache keeps (64 samples of 1032 x 1536, 8 rows: 86 and 66; below it, 24 of
+  //     1028 x 1536, 4 rows: 27 and 32; 64 of 1028 x 512, 4 rows: 24 and 33).
   const int want = rows >= 64 * 512 ? 64 : rows >= 32 * 512 ? 32 : rows >= 8 * 512 ? 8 : 4;
   for (int per : {want, 8, 4})
     if (per <= want && usable(per)) {
