@@ -479,14 +479,16 @@ def test_fused_qkv_epilogue_odd_heads(gpu_lib, heads):
 
 
 @pytest.mark.timeout(900)
-def test_flux_single_block_full_width(gpu_lib):
+@pytest.mark.parametrize("B", [4, 3])
+def test_flux_single_block_full_width(gpu_lib, B):
     """One Flux-shaped single-stream block at full width (H=3072, fused H -> 3H + F projection,
-    two-source [attention | MLP] -> H projection with 15360 inputs) on B=4 samples of 1024 image
-    + 512 text tokens: both projections run on the 256 x 256 GEMM tile, the second one switching
-    its A source mid-K.  The oracle recomputes two whole samples."""
+    two-source [attention | MLP] -> H projection with 15360 inputs) on B samples of 1024 image
+    + 512 text tokens: the first projection runs on 256 x 256 tiles, the second one switches
+    its A source mid-K on 192 x 256 tiles whose last round is split along K (B = 4: 384 of them)
+    or on 256 x 256 ones (B = 3: 216).  The oracle recomputes two whole samples."""
     base = C.FLUX_BLOCK
     m = base.model.replace(n_dual=0, n_single=1)
-    w = C.Workload(**{**base.__dict__, "name": "flux-single-block-B4", "index": 15, "model": m, "group": 4,
+    w = C.Workload(**{**base.__dict__, "name": f"flux-single-block-B{B}", "index": 15, "model": m, "group": B,
                       "grid": (1, 32, 32)})
     say("full-width single block: generating inputs")
     W, txt, cond, x0, eps = _inputs(w)
@@ -496,7 +498,7 @@ def test_flux_single_block_full_width(gpu_lib):
     res = ro.run(X0, T, E, cond=Cd, txt_out=torch.empty_like(T))
     torch.cuda.synchronize()
     v = host(res.vs[0])
-    for b in (0, 3):
+    for b in (0, B - 1):
         say("oracle sample", b)
         img, _ = odit.forward(m, W, x0[b:b + 1], txt[b:b + 1], cond=cond[b:b + 1], grid=w.grid)
         check(v[b:b + 1], img, C.BF16, model_stages(m), what=f"{w.name} v sample {b}")

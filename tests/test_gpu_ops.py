@@ -24,11 +24,11 @@ LIN = [
 ]
 
 
-# Shapes with at least one 256 x 256 tile per CU: these take the large-tile kernel.
-# (5000, 4000): 20 x 16 tiles, whole sixteens of tile columns (the XCD-blocked tile order) with a
-# partial last group of tile rows and ragged edges.
-LIN_LARGE = [(4133, 4133, 192, C.BF16), (8197, 2088, 128, C.BF16), (8200, 2100, 64, C.BF16),
-             (5000, 4000, 128, C.BF16)]
+# Shapes of two rounds of 192 x 256 tiles and, in the second line, of one or two of 256 x 256 ones, ragged edges.
+# (5000, 4000) and (7930, 4090) have whole sixteens of tile columns (the XCD-blocked tile order), 27 and 31 tile
+# rows with a partial last group; (3800, 4133) has 15 x 17 tiles, (7160, 2100) 28 x 9: one round.
+LIN_LARGE = [(4133, 4133, 192, C.BF16), (8197, 2088, 128, C.BF16), (8200, 2100, 64, C.BF16), (5000, 4000, 128, C.BF16),
+             (7930, 4090, 128, C.BF16), (3800, 4133, 192, C.BF16), (7160, 2100, 64, C.BF16)]
 
 
 @pytest.mark.parametrize("M,N,K,dt", LIN + LIN_LARGE)
